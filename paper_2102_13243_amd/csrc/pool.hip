@@ -460,52 +460,148 @@ __global__ __launch_bounds__(256) void round_bf16_kernel(const float* __restrict
   for (long long j = n4 * 4 + (long long)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += stride) dst[j] = f32_to_bf16(src[j]);
 }
 
-// y[j, :] = x[index[j], :]; a thread copies one element, adjacent threads adjacent columns
-template <typename T>
+// y[j, :] = x[index[j], :]; a thread copies V adjacent columns (16 bytes where rows are multiples of 16 bytes)
+template <typename T, int V>
 __global__ __launch_bounds__(256) void gather_rows_fwd_kernel(const T* __restrict__ x, const int32_t* __restrict__ index,
-                                                              T* __restrict__ y, int rows, int cols, long long total) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+                                                              T* __restrict__ y, int rows, unsigned cols, unsigned total) {
+  const unsigned i = blockIdx.x * 256u + threadIdx.x, cv = cols / V;  // total = count * cv < 2^31
   if (i >= total) return;
-  const long long j = i / cols;
-  const int col = (int)(i - j * cols);
+  const unsigned j = i / cv, col = (i - j * cv) * V;
   const int r = index[j];
-  y[i] = (r >= 0 && r < rows) ? x[(long long)r * cols + col] : from_f32<T>(0.f);
+  Pack<T, V> v;
+#pragma unroll
+  for (int e = 0; e < V; ++e) v.set(e, 0.f);
+  if (r >= 0 && r < rows) v = ldp<T, V>(x + (size_t)r * cols + col);
+  stp<T, V>(y + (size_t)j * cols + col, v);
 }
-// dx[index[j], :] += dy[j, :] for j = 0, 1, ... in that order: a thread owns one column and walks the gathered
-// rows, so a row that is named twice receives its two contributions in a fixed order, and only the named rows of
-// dx are read or written: count * cols element updates whatever the size of dx.
-template <typename T>
+
+// dx[index[j], :] += dy[j, :] for j = 0, 1, ... in that order.  Only additions into one row have an order to keep, so
+// the rows of dx are dealt to workgroups (bins) by a hash.  A workgroup reads the whole index, 4096 entries at a
+// time, and packs the entries of its own rows, in order, into LDS; then each wavefront takes entries that are the
+// first of their row in the list, adds the row's contributions in order (columns across the lanes) and
+// writes the row once.  Latency bound: about eight entries per bin, so that the scan of the index (count * 4 bytes
+// per bin, from L2) and the chains of rows are both short.  (One thread per column walking all of the index,
+// before: 2600 us for 8192 rows of 128 floats, one memory latency per row.)
+constexpr int GATHER_CHUNK = 4096;
+template <typename T, int V>
 __global__ __launch_bounds__(256) void gather_rows_vjp_kernel(const T* __restrict__ dy, const int32_t* __restrict__ index,
-                                                              T* dx, int rows, int cols, int count) {
-  const int col = blockIdx.x * blockDim.x + threadIdx.x;
-  if (col >= cols) return;
-  for (int j = 0; j < count; ++j) {
-    const int r = index[j];
-    if (r < 0 || r >= rows) continue;
-    T* p = dx + (long long)r * cols + col;
-    *p = from_f32<T>(to_f32<T>(*p) + to_f32<T>(dy[(long long)j * cols + col]));
+                                                              T* __restrict__ dx, int rows, int cols, int count, int shift) {
+  constexpr int PER = GATHER_CHUNK / 256;  // adjacent entries per thread
+  __shared__ int list_j[GATHER_CHUNK], list_r[GATHER_CHUNK];
+  __shared__ int wave_total[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const unsigned bin = blockIdx.x;
+  for (int base = 0; base < count; base += GATHER_CHUNK) {
+    const int j0 = base + threadIdx.x * PER;
+    int r[PER];
+#pragma unroll
+    for (int q = 0; q < PER / 4; ++q) {
+      if (j0 + 4 * q + 3 < count) {
+        const int4 v = *reinterpret_cast<const int4*>(index + j0 + 4 * q);
+        r[4 * q] = v.x; r[4 * q + 1] = v.y; r[4 * q + 2] = v.z; r[4 * q + 3] = v.w;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[4 * q + e] = j0 + 4 * q + e < count ? index[j0 + 4 * q + e] : -1;
+      }
+    }
+    unsigned mine = 0;
+#pragma unroll
+    for (int e = 0; e < PER; ++e)
+      if (r[e] >= 0 && r[e] < rows && (unsigned)(((unsigned)r[e] * 2654435761u) >> shift) == bin) mine |= 1u << e;
+    // position of this thread's entries: an inclusive scan of the counts over the wavefront, then over the wavefronts
+    const int n = __popc(mine);
+    int scan = n;
+    for (int off = 1; off < 64; off <<= 1) {
+      const int up = __shfl_up(scan, off, 64);
+      if (lane >= off) scan += up;
+    }
+    if (lane == 63) wave_total[wave] = scan;
+    __syncthreads();
+    int pos = scan - n, total = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      if (w < wave) pos += wave_total[w];
+      total += wave_total[w];
+    }
+#pragma unroll
+    for (int e = 0; e < PER; ++e)
+      if (mine & (1u << e)) { list_j[pos] = j0 + e; list_r[pos] = r[e]; ++pos; }
+    __syncthreads();
+    for (int i = wave; i < total; i += 4) {
+      const int row = list_r[i];
+      bool seen = false;  // by an earlier entry of the list, whose wavefront then adds this one too
+      for (int k = 0; k < i && !seen; k += 64) seen = __any(k + lane < i && list_r[k + lane] == row);
+      if (seen) continue;
+      for (int c0 = 0; c0 < cols; c0 += 64 * V) {
+        const int col = c0 + lane * V;
+        const bool live = col < cols;
+        T* p = dx + (size_t)row * cols + col;
+        Pack<T, V> acc;
+        if (live) acc = ldp<T, V>(p);
+        for (int k = i; k < total; k += 64) {
+          unsigned long long m = __ballot(k + lane < total && list_r[k + lane] == row);
+          while (m) {  // four contributions in flight, added one after another
+            Pack<T, V> d[4];
+            int have = 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              if (m) {
+                const int j = list_j[k + __builtin_ctzll(m)];
+                m &= m - 1;
+                if (live) d[u] = ldp<T, V>(dy + (size_t)j * cols + col);
+                ++have;
+              }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (u < have) {
+                float o[V];
+#pragma unroll
+                for (int e = 0; e < V; ++e) o[e] = acc.get(e) + d[u].get(e);
+                acc = pack_of<T, V>(o);  // rounded to the storage type after every addition
+              }
+          }
+        }
+        if (live) stp<T, V>(p, acc);
+      }
+    }
+    __syncthreads();  // the list is free again, and this chunk's rows are visible to the whole workgroup
   }
 }
 
 }  // namespace
 
+// 16-byte accesses need rows that are multiples of 16 bytes
+#define GATHER_LAUNCH(KERNEL, grid, ...)                                                                        \
+  do {                                                                                                          \
+    if (d.dtype == S4TF_BF16) {                                                                                 \
+      typedef bf16_t T;                                                                                         \
+      if (V > 1) hipLaunchKernelGGL((KERNEL<T, 8>), dim3(grid), dim3(256), 0, st, __VA_ARGS__);                 \
+      else hipLaunchKernelGGL((KERNEL<T, 1>), dim3(grid), dim3(256), 0, st, __VA_ARGS__);                       \
+    } else {                                                                                                    \
+      typedef float T;                                                                                          \
+      if (V > 1) hipLaunchKernelGGL((KERNEL<T, 4>), dim3(grid), dim3(256), 0, st, __VA_ARGS__);                 \
+      else hipLaunchKernelGGL((KERNEL<T, 1>), dim3(grid), dim3(256), 0, st, __VA_ARGS__);                       \
+    }                                                                                                           \
+  } while (0)
+
+static int gather_vec(const s4tf_gather_desc& d) {
+  const int v = d.dtype == S4TF_BF16 ? 8 : 4;
+  return d.cols % v ? 1 : v;
+}
 int gather_rows_fwd(const s4tf_gather_desc& d, const void* x, const int32_t* index, void* y, hipStream_t st) {
   ProfScope ps(PC_ELEMENTWISE, st);
-  const long long total = (long long)d.count * d.cols;
-  const unsigned blocks = (unsigned)((total + 255) / 256);
-  if (d.dtype == S4TF_BF16)
-    hipLaunchKernelGGL(gather_rows_fwd_kernel<bf16_t>, dim3(blocks), dim3(256), 0, st, (const bf16_t*)x, index, (bf16_t*)y, d.rows, d.cols, total);
-  else
-    hipLaunchKernelGGL(gather_rows_fwd_kernel<float>, dim3(blocks), dim3(256), 0, st, (const float*)x, index, (float*)y, d.rows, d.cols, total);
+  const int V = gather_vec(d);
+  const unsigned total = (unsigned)((long long)d.count * (d.cols / V));
+  GATHER_LAUNCH(gather_rows_fwd_kernel, (total + 255) / 256, (const T*)x, index, (T*)y, d.rows, (unsigned)d.cols, total);
   return launch_status("gather_rows_fwd");
 }
 int gather_rows_vjp(const s4tf_gather_desc& d, const void* dy, const int32_t* index, void* dx, hipStream_t st) {
   ProfScope ps(PC_ELEMENTWISE, st);
-  const unsigned blocks = (unsigned)((d.cols + 255) / 256);
-  if (d.dtype == S4TF_BF16)
-    hipLaunchKernelGGL(gather_rows_vjp_kernel<bf16_t>, dim3(blocks), dim3(256), 0, st, (const bf16_t*)dy, index, (bf16_t*)dx, d.rows, d.cols, d.count);
-  else
-    hipLaunchKernelGGL(gather_rows_vjp_kernel<float>, dim3(blocks), dim3(256), 0, st, (const float*)dy, index, (float*)dx, d.rows, d.cols, d.count);
+  const int V = gather_vec(d);
+  int log_bins = 1;  // a bin for about 8 entries, at most 1024 bins: each reads the whole index
+  while (log_bins < 10 && (8 << log_bins) < d.count) ++log_bins;
+  GATHER_LAUNCH(gather_rows_vjp_kernel, 1u << log_bins, (const T*)dy, index, (T*)dx, d.rows, d.cols, d.count, 32 - log_bins);
   return launch_status("gather_rows_vjp");
 }
 

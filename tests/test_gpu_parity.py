@@ -1007,6 +1007,39 @@ def test_gather_rows_and_its_inout_pullback(rows, cols, count, bf16):
     np.testing.assert_array_equal(to_host(dx)[untouched], np.asarray(base, np.float64)[untouched])
 
 
+@pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
+@pytest.mark.parametrize("rows,cols,count", [
+    (37, 16, 9000),       # every row named hundreds of times, more than two rounds of the index
+    (100000, 67, 4097),   # element-wise columns, one entry beyond a round
+    (3, 1, 8192), (1, 300, 4096), (5000, 520, 300), (200000, 8, 20000)])
+def test_gather_rows_pullback_keeps_the_order_of_repeated_rows(rows, cols, count, bf16):
+    """Exactly the additions dx[index[j]] += dy[j] in order of j, each rounded to the storage type; entries out of range
+    change nothing."""
+    rng = np.random.default_rng(rows + count)
+    idx = rng.integers(0, rows, count).astype(np.int32)
+    idx[::17] = np.where(rng.random(len(idx[::17])) < 0.5, -1, rows)
+    dy, base = grid(rng.standard_normal((count, cols)), bf16), grid(rng.standard_normal((rows, cols)), bf16)
+    want = base.copy()
+    ok = np.flatnonzero((idx >= 0) & (idx < rows))
+    order = ok[np.argsort(idx[ok], kind="stable")]
+    rank = np.empty(count, np.int64)  # the how-manieth naming of its row an entry is
+    first = np.searchsorted(idx[order], idx[order], side="left")
+    rank[order] = np.arange(len(order)) - first
+    for k in range(int(rank[ok].max()) + 1):
+        sel = ok[rank[ok] == k]
+        want[idx[sel]] = grid(want[idx[sel]] + dy[sel], bf16)
+    d = B.GatherDesc(rows, cols, count, B.S4TF_BF16 if bf16 else B.S4TF_F32)
+    dx = empty((rows, cols), bf16)
+    dx.copy_(to_dev(base, bf16))
+    B.s4tf_gather_rows_vjp(d, to_dev(dy, bf16), to_dev(idx, dtype=np.int32), dx)
+    np.testing.assert_array_equal(to_host(dx), want.astype(np.float64))
+    y = empty((count, cols), bf16)
+    B.s4tf_gather_rows_fwd(d, to_dev(base, bf16), to_dev(idx, dtype=np.int32), y)
+    expect = np.zeros((count, cols))
+    expect[ok] = base[idx[ok]]
+    np.testing.assert_array_equal(to_host(y), expect)
+
+
 # ---- BatchNorm in inference mode: running statistics, folding into the convolution -----------------------------
 @pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
 @pytest.mark.parametrize("shape,act,use_bias", [((4, 14, 14, 64, 128, 3, 1, 1), "relu", False),
