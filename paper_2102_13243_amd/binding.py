@@ -165,10 +165,20 @@ def _nbytes(t):
     return 0 if t is None else t.numel() * t.element_size()
 
 
+_current_stream = None
+
+
 def _stream(stream):
+    global _current_stream
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        # the raw handle of torch's current stream: without the stream object that torch.cuda.current_stream() builds
+        # around it (2.5 us of a 5 us call)
+        if _current_stream is None:
+            import torch
+            torch.cuda.current_stream()  # initialises torch's side of the device
+            raw, device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+            _current_stream = lambda: raw(device())
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
