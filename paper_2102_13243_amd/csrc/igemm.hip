@@ -425,7 +425,7 @@ __device__ inline void mma_tile(const T* As, const T* Bs, int arow, int brow, in
 // workgroups share a CU: for GEMMs whose k-loop is a handful of tiles, where what hides the load latency is
 // other workgroups and not this one's own pipeline.
 template <typename T, int PASS, bool VECMODE, int WM, int WN, int FM, int FN, int BK_, int WK = 1, int NBUF = 2>
-__global__ __launch_bounds__(NT) void igemm_kernel(const Args a) {
+__global__ __launch_bounds__(NT, sizeof(T) == 4 ? 2 : 1) void igemm_kernel(const Args a) {
   static_assert(WM * WN * WK == 4, "four wavefronts");
   static_assert(WK == 1 || sizeof(T) == 4, "the k split over wavefronts is for the fp32 epilogue only");
   constexpr int BM = WM * FM * 32, BN = WN * FN * 32;
@@ -716,19 +716,6 @@ template <typename T> bool vec_ok(const ConvGeom& g) {
   return g.C % Cfg<T>::VEC == 0 && g.K % Cfg<T>::VEC == 0;
 }
 
-// x / d for 0 <= x < 2^31 and d >= 1 as (mulhi(x, magic) + x) >> shift, with shift = ceil(log2 d) and
-// magic = ceil(2^(32+shift) / d) - 2^32: the round-up error of the 33-bit multiplier is below d <= 2^shift,
-// which makes the quotient exact for every 32-bit x; d == 1 gives magic 0, shift 0, and no special case.
-void magic_div(int d, uint32_t& magic, int& shift) {
-  if (d < 1) d = 1;
-  int s = 0;
-  while ((1LL << s) < d) ++s;
-  const unsigned __int128 one = 1;
-  const unsigned __int128 m = ((one << (32 + s)) + (unsigned)d - 1) / (unsigned)d;
-  magic = (uint32_t)(m - (one << 32));
-  shift = s;
-}
-
 void fill_sizes(Args& a, int pass, int dtype) {
   const ConvGeom& g = a.g;
   const unsigned long long es = dtype_size(dtype);
@@ -867,6 +854,19 @@ void wgrad_split(const ConvGeom& g, int dtype, int& splits, int& nk_per_split) {
 
 }  // namespace
 
+// x / d for 0 <= x < 2^31 and d >= 1 as (mulhi(x, magic) + x) >> shift, with shift = ceil(log2 d) and
+// magic = ceil(2^(32+shift) / d) - 2^32: the round-up error of the 33-bit multiplier is below d <= 2^shift,
+// which makes the quotient exact for every 32-bit x; d == 1 gives magic 0, shift 0, and no special case.
+void magic_div(int d, uint32_t& magic, int& shift) {
+  if (d < 1) d = 1;
+  int s = 0;
+  while ((1LL << s) < d) ++s;
+  const unsigned __int128 one = 1;
+  const unsigned __int128 m = ((one << (32 + s)) + (unsigned)d - 1) / (unsigned)d;
+  magic = (uint32_t)(m - (one << 32));
+  shift = s;
+}
+
 int igemm_fwd(const ConvGeom& g, int dtype, const void* x, const void* w, const float* bias, int act,
               void* y, hipStream_t st, float* stats_part, int* stats_rows) {
   Args a = {};
@@ -889,6 +889,9 @@ int igemm_fwd(const ConvGeom& g, int dtype, const void* x, const void* w, const 
   const bool with_stats = stats_part && stats_rows && !bias && act == S4TF_ACT_NONE;
   if (patchconv_fwd_ok(g, dtype) && aligned16(x) && aligned16(w) && aligned16(y))  // few channels, 3x3: out of an LDS patch
     return patchconv_fwd(g, x, w, bias, act, y, with_stats ? stats_part : nullptr, with_stats ? stats_rows : nullptr, st);
+  if (wave_gemm_ok(PASS_FWD, g, dtype) && aligned16(x) && aligned16(w) && aligned16(y))
+    return wave_gemm_fwd(g, static_cast<const float*>(x), static_cast<const float*>(w), bias, act, static_cast<float*>(y),
+                      with_stats ? stats_part : nullptr, with_stats ? stats_rows : nullptr, st);
   if (with_stats) *stats_rows = 32;
   fill_tiles_f32(a, false);
   if (with_stats) a.stats = stats_part;
@@ -969,13 +972,15 @@ int igemm_dgrad(const ConvGeom& g, int dtype, const void* dy, const void* w, voi
   }
   if (patchconv_dgrad_ok(g, dtype) && aligned16(dy) && aligned16(w) && aligned16(dx))
     return patchconv_dgrad(g, dy, w, dx, accumulate, st);
+  if (wave_gemm_ok(PASS_DGRAD, g, dtype) && aligned16(dy) && aligned16(w) && aligned16(dx))
+    return wave_gemm_dgrad(g, static_cast<const float*>(dy), static_cast<const float*>(w), static_cast<float*>(dx), accumulate, st);
   fill_tiles_f32(a, false);
   return launch<float, PASS_DGRAD>(a, 1, st);
 }
 
 size_t igemm_wgrad_workspace(const ConvGeom& g, int dtype) {
   int splits, per;
-  if (patchconv_wgrad_ok(g, dtype)) splits = patchconv_wgrad_splits(g);
+  if (wave_gemm_ok(PASS_WGRAD, g, dtype)) splits = wave_gemm_wgrad_splits(g);
   else wgrad_split(g, dtype, splits, per);
   if (splits <= 1) return 0;
   return (size_t)splits * g.R * g.S * g.C * g.K * sizeof(float);
@@ -988,18 +993,17 @@ int igemm_wgrad(const ConvGeom& g, int dtype, const void* x, const void* dy, flo
   a.Mg = g.R * g.S * g.C; a.Ng = g.K; a.Kg = g.N * g.P * g.Q;
   a.simple = (g.R == 1 && g.S == 1 && g.stride == 1 && g.pad == 0);
   fill_sizes(a, PASS_WGRAD, dtype);
-  // few channels, 3x3, small images: out of an LDS patch
-  const bool patch = patchconv_wgrad_ok(g, dtype) && aligned16(x) && aligned16(dy) && aligned16(dw) && aligned16(ws);
+  const bool waves = wave_gemm_ok(PASS_WGRAD, g, dtype) && aligned16(x) && aligned16(dy) && aligned16(dw) && aligned16(ws);
   int splits, per = 0;
-  if (patch) splits = patchconv_wgrad_splits(g);
+  if (waves) splits = wave_gemm_wgrad_splits(g);
   else wgrad_split(g, dtype, splits, per);
   const long long n = (long long)a.Mg * a.Ng;
   if (splits > 1 && ws_bytes < (size_t)splits * n * sizeof(float))
     return fail(S4TF_ERR_WORKSPACE, "wgrad needs %zu workspace bytes, got %zu", (size_t)splits * n * sizeof(float), ws_bytes);
   int rc;
-  if (patch) {
+  if (waves) {
     ProfScope ps(PC_CONV_WGRAD, st);
-    rc = patchconv_wgrad(g, x, dy, splits > 1 ? static_cast<float*>(ws) : dw, splits, st);
+    rc = wave_gemm_wgrad(g, static_cast<const float*>(x), static_cast<const float*>(dy), splits > 1 ? static_cast<float*>(ws) : dw, st);
   } else {
     if (dtype == S4TF_BF16) fill_tiles(a, 128, 128, Cfg<bf16_t>::BK);
     else fill_tiles_f32(a, true);

@@ -47,6 +47,7 @@ struct Args {
   int shiftC, shiftK, shiftS;
 };
 
+void magic_div(int d, uint32_t& magic, int& shift);
 // x / d for 0 <= x < 2^31 with the host-computed (magic, shift) of d (magic_div in igemm.hip)
 __device__ inline int div_magic(int x, uint32_t magic, int shift) {
   return (int)((__umulhi((uint32_t)x, magic) + (uint32_t)x) >> shift);
@@ -82,5 +83,13 @@ bool igemm_dma_geom_ok(int pass, const ConvGeom& g);                     // shap
 bool igemm_dma_ok(int pass, const ConvGeom& g, const Args& a);            // shape and pointer alignment
 void igemm_dma_tile(int pass, int Mg, int Ng, int splits, int& BM, int& BN);  // the tile igemm_dma_launch picks
 int igemm_dma_launch(int pass, Args& a, int splits, hipStream_t st);
+
+// fp32, channel counts that are multiples of 4 (wave_gemm.hip)
+bool wave_gemm_ok(int pass, const ConvGeom& g, int dtype);
+int wave_gemm_fwd(const ConvGeom& g, const float* x, const float* w, const float* bias, int act, float* y, float* stats,
+                  int* stats_rows, hipStream_t st);
+int wave_gemm_dgrad(const ConvGeom& g, const float* dy, const float* w, float* dx, int accumulate, hipStream_t st);
+int wave_gemm_wgrad_splits(const ConvGeom& g);
+int wave_gemm_wgrad(const ConvGeom& g, const float* x, const float* dy, float* out, hipStream_t st);
 
 }  // namespace s4tf

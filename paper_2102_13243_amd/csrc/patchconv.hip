@@ -48,7 +48,7 @@ struct PatchArgs {
 // layers of an inverted-residual block and, with FLIP, the pullback of its projection layers): the "patch" is the
 // tile's 128 pixels themselves, whatever the image shape.
 template <int CI, int CO, bool FLIP, int TAPS = 9>
-__global__ __launch_bounds__(256) void patchconv_kernel(const PatchArgs a) {
+__global__ __launch_bounds__(256, 2) void patchconv_kernel(const PatchArgs a) {
   constexpr int G = 2;  // blocks of 16 pixels per wavefront
   constexpr int CS = CI + 4;                                 // floats per patch pixel
   constexpr int WS = CO == 16 ? 16 : CO == 32 ? 48 : 80;     // floats per filter row: 16 or 48 modulo the 64 banks
@@ -219,146 +219,6 @@ __global__ __launch_bounds__(256) void patchconv_kernel(const PatchArgs a) {
   }
 }
 
-// ---- filter gradient ------------------------------------------------------------------------------------
-// dw[tap][c][k] = sum over pixels m of x[m + tap][c] * dy[m][k]: per tap a (CI x pixels) x (pixels x CO) product,
-// with the MFMA's k axis running over 4 adjacent pixels of an image row: A: lane l = channel l%16, pixel l/16 (read
-// from the patch, 16 adjacent channels per pixel); B: lane l = pixel l/16, output l%16 (from the tile's rows of dy);
-// D: register v of lane l = channel 4*(l/16) + v, output l%16.  A wavefront keeps one accumulator block per tap
-// through all the tiles its workgroup walks; the workgroup then writes one partial filter gradient (its slab), and
-// a reduction kernel adds the slabs in a fixed order.
-// Patch pixels are 16 (48, 80) floats apart for 16 (32, 64) channels and rows of dy 16 (48) floats: 4 adjacent
-// pixels x 16 adjacent channels then cover the 64 LDS banks once.
-struct WgradArgs {
-  const float* x;   // (N, H, W, CI)
-  const float* dy;  // (N, H, W, KT)
-  float* out;       // gridDim.x slabs of (3, 3, CI, KT)
-  int N, H, W, KT, RH, IMGS, tiles;
-  long long slab;   // floats per slab
-};
-
-template <int CI, int CO>
-__global__ __launch_bounds__(256) void patchconv_wgrad_kernel(const WgradArgs a) {
-  constexpr int CS = CI == 16 ? 16 : CI == 32 ? 48 : 80;
-  constexpr int DS = CO == 16 ? 16 : 48;
-  constexpr int NCB = CI / 16, NKB = CO / 16, C4 = CI / 4, K4 = CO / 4;
-  // Four blocks of 16 x 16 outputs: a wavefront owns one of them over all 128 pixels (nothing to add across
-  // wavefronts).  One block: a wavefront owns 32 of the pixels, and the four are added through LDS at the end.
-  constexpr bool OWN_BLOCK = NCB * NKB == 4;
-  static_assert(OWN_BLOCK || NCB * NKB == 1, "one or four output blocks per workgroup");
-  constexpr int STEPS = OWN_BLOCK ? TILE / 4 : TILE / 16;  // k-steps of 4 pixels per wavefront and tile
-  constexpr int TILE_FLOATS = PATCH_PIXELS * CS + TILE * DS, RED_FLOATS = OWN_BLOCK ? 0 : 9 * CI * CO;
-  __shared__ __attribute__((aligned(16))) float smem[TILE_FLOATS > RED_FLOATS ? TILE_FLOATS : RED_FLOATS];
-  float* patch = smem;
-  float* dyt = smem + PATCH_PIXELS * CS;
-  const int H = a.H, W = a.W, PW = W + 2, RH = a.RH, PR = RH + 2, KT = a.KT, n0 = blockIdx.y * CO;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int cb0 = OWN_BLOCK ? wave / NKB : 0, kb0 = OWN_BLOCK ? wave % NKB : 0;
-  const int m0 = (OWN_BLOCK ? 0 : wave * 32) + (lane >> 4);  // this lane's pixel of k-step 0
-  const int lw = 31 - __clz(W), lrh = a.IMGS > 1 ? 31 - __clz(RH) : 30;  // W and RH (if several images) are powers of two
-  // patch offset of tile pixel m at this lane's channel: patch row = row + 2*image
-  auto pix_off = [&](int m) {
-    const int row = m >> lw;
-    return ((row + 2 * (row >> lrh)) * PW + (m & (W - 1))) * CS + cb0 * 16 + (lane & 15);
-  };
-  const int bbase = m0 * DS + kb0 * 16 + (lane & 15);
-  f32x4 acc[9];
-#pragma unroll
-  for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  constexpr int PV = (PATCH_PIXELS * C4 + 255) / 256, DV = (TILE * K4 + 255) / 256;
-  const int chunks = a.IMGS * PR * PW * C4;
-  for (int tile = blockIdx.x; tile < a.tiles; tile += gridDim.x) {
-    int n, p0;
-    if (a.IMGS == 1) {
-      const int tiles_per_image = H / RH;
-      n = tile / tiles_per_image;
-      p0 = (tile - n * tiles_per_image) * RH;
-    } else {
-      n = tile * a.IMGS;
-      p0 = 0;
-    }
-    float4 pv[PV], dv[DV];
-#pragma unroll
-    for (int k = 0; k < PV; ++k) {
-      const int i = threadIdx.x + k * 256;
-      const int c4 = i % C4, t = i / C4, pw = t % PW, prow = t / PW, img = prow / PR, pr = prow - img * PR;
-      const int h = p0 + pr - 1, wc = pw - 1;
-      pv[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (i < chunks && h >= 0 && h < H && wc >= 0 && wc < W)
-        pv[k] = *reinterpret_cast<const float4*>(a.x + (((long long)(n + img) * H + h) * W + wc) * CI + c4 * 4);
-    }
-#pragma unroll
-    for (int k = 0; k < DV; ++k) {
-      const int i = threadIdx.x + k * 256;
-      const int k4 = i % K4, m = i / K4;
-      dv[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (i < TILE * K4) dv[k] = *reinterpret_cast<const float4*>(a.dy + ((long long)tile * TILE + m) * KT + n0 + k4 * 4);
-    }
-    __syncthreads();  // everyone is done with the previous tile
-#pragma unroll
-    for (int k = 0; k < PV; ++k) {
-      const int i = threadIdx.x + k * 256;
-      if (i < chunks) *reinterpret_cast<float4*>(patch + (i / C4) * CS + (i % C4) * 4) = pv[k];
-    }
-#pragma unroll
-    for (int k = 0; k < DV; ++k) {
-      const int i = threadIdx.x + k * 256;
-      if (i < TILE * K4) *reinterpret_cast<float4*>(dyt + (i / K4) * DS + (i % K4) * 4) = dv[k];
-    }
-    __syncthreads();
-    // the fragments of k-step j+1 are read while step j is multiplied
-    float af[2][9], bf[2];
-    auto read_step = [&](int j, int buf) {
-      bf[buf] = dyt[bbase + 4 * j * DS];
-      const int ab = pix_off(m0 + 4 * j);
-#pragma unroll
-      for (int t = 0; t < 9; ++t) af[buf][t] = patch[ab + ((t / 3) * PW + (t % 3)) * CS];
-    };
-    // (a rolled loop of two steps: unrolled all the way, the compiler reads every step's fragments up front and
-    // the registers they fill leave one wavefront per SIMD)
-    static_assert(STEPS % 2 == 0, "steps go in pairs");
-    read_step(0, 0);
-#pragma unroll 1
-    for (int j = 0; j < STEPS; j += 2) {
-      read_step(j + 1, 1);
-#pragma unroll
-      for (int t = 0; t < 9; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[0][t], bf[0], acc[t], 0, 0, 0);
-      if (j + 2 < STEPS) read_step(j + 2, 0);
-#pragma unroll
-      for (int t = 0; t < 9; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[1][t], bf[1], acc[t], 0, 0, 0);
-    }
-  }
-  float* slab = a.out + (long long)blockIdx.x * a.slab;
-  if constexpr (OWN_BLOCK) {
-#pragma unroll
-    for (int t = 0; t < 9; ++t)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        slab[(long long)(t * CI + cb0 * 16 + 4 * (lane >> 4) + v) * KT + n0 + kb0 * 16 + (lane & 15)] = acc[t][v];
-  } else {
-    // the four wavefronts' sums, added in wavefront order
-    __syncthreads();
-    float* red = smem;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      if (wave == w) {
-#pragma unroll
-        for (int t = 0; t < 9; ++t)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            float* r = red + (t * CI + 4 * (lane >> 4) + v) * CO + (lane & 15);
-            *r = w == 0 ? acc[t][v] : *r + acc[t][v];
-          }
-      }
-      __syncthreads();
-    }
-    for (int i = threadIdx.x; i < 9 * CI * K4; i += 256) {
-      const int row = i / K4, k4 = i - row * K4;  // row = (tap, c)
-      *reinterpret_cast<float4*>(slab + (long long)row * KT + n0 + k4 * 4) = *reinterpret_cast<const float4*>(red + row * CO + k4 * 4);
-    }
-  }
-}
-
 template <int CI, int CO, bool FLIP, int TAPS = 9>
 int launch_patch(const PatchArgs& a, hipStream_t st) {
   const unsigned tiles = (unsigned)((long long)a.N * a.H * a.W / TILE);
@@ -454,34 +314,6 @@ int patchconv_dgrad(const ConvGeom& g, const void* dy, const void* w, void* dx, 
   if (g.C == 16) return launch_patch<16, 16, true>(a, st);
   if (g.C == 32) return launch_patch<32, 32, true>(a, st);
   return launch_patch<64, 16, true>(a, st);
-}
-
-bool patchconv_wgrad_ok(const ConvGeom& g, int dtype) { return dtype == S4TF_F32 && shape_ok(g) && channels_ok(g.C, g.K); }
-
-// Workgroups along the pixel axis = partial filter gradients (slabs) the kernel leaves: enough workgroups to fill
-// the chip, each walking at most a few tiles
-int patchconv_wgrad_splits(const ConvGeom& g) {
-  const int tiles = (int)((long long)g.N * g.H * g.W / TILE);
-  const int per_tile = g.C == 64 ? 4 : 1;  // workgroups per tile: blocks of 16 output channels for 64-channel layers
-  int want = 512 / per_tile;
-  if (want > tiles) want = tiles;
-  const int walk = (tiles + want - 1) / want;
-  return (tiles + walk - 1) / walk;
-}
-
-// `splits` slabs of (3, 3, C, K) partial sums into out (the filter gradient itself when splits == 1)
-int patchconv_wgrad(const ConvGeom& g, const void* x, const void* dy, float* out, int splits, hipStream_t st) {
-  if (!aligned16(x) || !aligned16(dy) || !aligned16(out)) return fail(S4TF_ERR_SHAPE, "patchconv: operands must be 16-byte aligned");
-  WgradArgs a = {};
-  a.x = static_cast<const float*>(x); a.dy = static_cast<const float*>(dy); a.out = out;
-  a.N = g.N; a.H = g.H; a.W = g.W; a.KT = g.K;
-  tiling(g.N, g.H, g.W, a.RH, a.IMGS);
-  a.tiles = (int)((long long)g.N * g.H * g.W / TILE);
-  a.slab = (long long)9 * g.C * g.K;
-  if (g.C == 16) hipLaunchKernelGGL((patchconv_wgrad_kernel<16, 16>), dim3(splits, 1), dim3(256), 0, st, a);
-  else if (g.C == 32) hipLaunchKernelGGL((patchconv_wgrad_kernel<32, 32>), dim3(splits, 1), dim3(256), 0, st, a);
-  else hipLaunchKernelGGL((patchconv_wgrad_kernel<64, 16>), dim3(splits, 4), dim3(256), 0, st, a);
-  return launch_status("patchconv_wgrad");
 }
 
 }  // namespace s4tf

@@ -178,6 +178,20 @@ CONV_SHAPES = [
 ]
 
 
+# fp32 layers at the edges of the wavefront-tile GEMM: fewer rows than a tile, one k-step, ragged channels (multiples of 4
+# only), k-steps that end inside a tap, splits of the reduction axis over wavefronts and workgroups, stride 2 and 3
+WAVE_SHAPES = [
+    (1, 1, 1, 400, 4, 1, 1, 0), (3, 1, 1, 4, 132, 1, 1, 0), (1, 3, 3, 12, 20, 3, 1, 1), (2, 5, 7, 36, 68, 3, 2, 1),
+    (1, 33, 1, 16, 16, 3, 1, 1), (1, 2, 2, 1280, 8, 1, 1, 0), (3, 9, 11, 44, 132, 1, 1, 0), (2, 10, 10, 6, 16, 5, 1, 0),
+    (1, 13, 13, 28, 40, 3, 3, 1), (2, 40, 40, 16, 16, 3, 1, 1), (9, 20, 20, 32, 64, 3, 1, 1), (1, 64, 64, 64, 96, 1, 1, 0),
+]
+
+
+@pytest.mark.parametrize("shape", WAVE_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_conv2d_wavefront_tiles(shape):
+    test_conv2d_fwd_and_vjp(shape, False)
+
+
 def _random_conv_shapes(count, seed):
     """Seeded shapes drawn from the values at which the library switches kernels (channel counts around the
     loaders' vector widths and the LDS-patch kernel's 16/24/32/64, image sizes around its 8/16/32-wide tiles,
