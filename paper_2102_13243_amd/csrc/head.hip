@@ -1,25 +1,235 @@
-// Head of the network: global average pool + dense + mean softmax cross-entropy, value and
-// pullback in one call (`softmaxCrossEntropy(logits:labels:)` of the paper's training loop).
-// Small and latency bound.  The dense part is three tiny fp32 GEMMs on the pooled [n,c] matrix.  The two
-// with few rows (logits, and the cotangent of the pooled features) would fill a handful of 128x128
-// tiles, so they run as split-k register-tiled GEMMs over ~256 workgroups whose partial sums the next
-// kernel in line adds up in a fixed order; dW reuses the implicit-GEMM wgrad kernel.
+// Head of the network: global average pool + dense + mean softmax cross-entropy, value and pullback in one call
+// (`softmaxCrossEntropy(logits:labels:)` of the paper's training loop).
 //   pbar = mean_{h,w} x;  z = pbar W + b;  loss = mean_n (logsumexp(z_n) - z_n[label_n])
 //   dz = (softmax(z) - onehot)/n;  dW = pbar^T dz;  db = sum_n dz;  dx = (dz W^T)/(h*w)
+// Latency bound throughout: the work is tiny, each kernel a few microseconds.  Two ways through it:
+//   * small heads (W of at most 32 KB): everything that concerns one sample, pooled features to dx, by one workgroup that
+//     keeps W in LDS; then one kernel for what sums over the batch (dW, db, loss).  2 launches instead of 9: the tiny
+//     block's head 85 -> 12 us, of which a single workgroup's pooling was 39;
+//   * others (1000 classes): pooling, two products on the wavefront-tile GEMM (logits with the bias in its epilogue,
+//     cotangent of the pooled features), softmax, dW on the same GEMM, one kernel for db and the loss.
+// What the parameters' gradients need is kept apart (head_params), so that a training step can run it on its second
+// stream.
 #include "s4tf_internal.h"
+#include "igemm_args.h"
+#include "pack.h"
 
 namespace s4tf {
 namespace {
 
-template <typename T>
-__global__ void gap_kernel(const T* __restrict__ x, float* __restrict__ pbar, int N, int HW, int C) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;  // (n, c)
-  if (i >= N * C) return;
-  int c = i % C, n = i / C;
-  const T* p = x + (long long)n * HW * C + c;
+constexpr int SMALL_W = 8192;      // floats of W a workgroup keeps in LDS
+constexpr int SMALL_X = 1 << 16;   // elements of a sample one workgroup pools
+constexpr int SMALL_C = 1024, SMALL_K = 256;
+
+// Sum over pixels of V channels per thread: threads (pixel lane, channel vector), the lanes added in order.
+// part: LDS, lanes * cvs * V floats; the result for channel c (of this block's cvs * V) ends up in part[c].
+template <typename T, int V>
+__device__ inline void pool_pixels(const T* __restrict__ x, int HW, int C, int cvs, int lanes, float* part) {
+  const int cv = threadIdx.x % cvs, pl = threadIdx.x / cvs;
+  float s[V];
+#pragma unroll
+  for (int e = 0; e < V; ++e) s[e] = 0.f;
+  if (pl < lanes) {
+    const T* p = x + cv * V;
+    int j = pl;
+    for (; j + 3 * lanes < HW; j += 4 * lanes) {
+      Pack<T, V> v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = ldp<T, V>(p + (long long)(j + u * lanes) * C);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int e = 0; e < V; ++e) s[e] += v[u].get(e);
+    }
+    for (; j < HW; j += lanes) {
+      const Pack<T, V> v = ldp<T, V>(p + (long long)j * C);
+#pragma unroll
+      for (int e = 0; e < V; ++e) s[e] += v.get(e);
+    }
+#pragma unroll
+    for (int e = 0; e < V; ++e) part[(pl * cvs + cv) * V + e] = s[e];
+  }
+  __syncthreads();
+  for (int c = threadIdx.x; c < cvs * V; c += blockDim.x) {
+    float t = 0.f;
+    for (int l = 0; l < lanes; ++l) t += part[l * cvs * V + c];
+    part[c] = t;  // read by this thread alone until the next barrier
+  }
+  __syncthreads();
+}
+
+// dx[hw][c] = dp[c] (LDS) for this block's cvs * V channels, added to what dx holds when it accumulates (one rounding)
+template <typename T, int V>
+__device__ inline void spread_pixels(const float* dp, T* dx, int HW, int C, int cvs, int lanes, int accumulate) {
+  const int cv = threadIdx.x % cvs, pl = threadIdx.x / cvs;
+  if (pl >= lanes) return;
+  float v[V];
+#pragma unroll
+  for (int e = 0; e < V; ++e) v[e] = dp[cv * V + e];
+  const Pack<T, V> o = pack_of<T, V>(v);
+  T* p = dx + cv * V;
+  for (int j = pl; j < HW; j += lanes) {
+    if (accumulate) {
+      const Pack<T, V> old = ldp<T, V>(p + (long long)j * C);
+      float w[V];
+#pragma unroll
+      for (int e = 0; e < V; ++e) w[e] = old.get(e) + v[e];
+      stp<T, V>(p + (long long)j * C, pack_of<T, V>(w));
+    } else {
+      stp<T, V>(p + (long long)j * C, o);
+    }
+  }
+}
+
+// over the 256 threads of a block; sh: 4 floats of LDS
+__device__ inline float block_max(float v, float* sh) {
+  for (int off = 1; off < 64; off <<= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  v = fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
+  __syncthreads();
+  return v;
+}
+__device__ inline float block_sum(float v, float* sh) {
+  for (int off = 1; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  v = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+  __syncthreads();
+  return v;
+}
+
+// one workgroup per sample: pooled features, logits, softmax, dz, and the sample's dx
+template <typename T, int V>
+__global__ __launch_bounds__(256) void head_sample_kernel(const T* __restrict__ x, const float* __restrict__ W,
+                                                          const float* __restrict__ b, const int32_t* __restrict__ labels,
+                                                          float* __restrict__ pbar, float* __restrict__ z, float* __restrict__ dz,
+                                                          float* __restrict__ rowloss, T* dx, int N, int HW, int C, int K,
+                                                          int accumulate) {
+  __shared__ float Wl[SMALL_W], part[SMALL_C > 256 * V ? SMALL_C : 256 * V], dzl[SMALL_K], red[256], sh[4];
+  const int n = blockIdx.x, t = threadIdx.x;
+  for (int i = t; i < C * K; i += 256) Wl[i] = W[i];
+  const int CV = C / V, lanes = 256 / CV;
+  if (lanes > 0) {
+    pool_pixels<T, V>(x + (long long)n * HW * C, HW, C, CV, lanes, part);
+  } else {  // more channel vectors than threads
+    for (int c = t; c < C; c += 256) {
+      float s = 0.f;
+      for (int j = 0; j < HW; ++j) s += to_f32<T>(x[((long long)n * HW + j) * C + c]);
+      part[c] = s;
+    }
+    __syncthreads();
+  }
+  const float hw = (float)HW;
+  for (int c = t; c < C; c += 256) {
+    part[c] /= hw;
+    pbar[n * C + c] = part[c];
+  }
+  __syncthreads();
+  // logits: 256 / K threads per class, added in order
+  const int parts = 256 / K, j = t % K, pt = t / K;
   float s = 0.f;
-  for (int j = 0; j < HW; ++j) s += to_f32<T>(p[(long long)j * C]);
-  pbar[i] = s / (float)HW;
+  if (pt < parts)
+    for (int c = pt; c < C; c += parts) s = fmaf(part[c], Wl[c * K + j], s);
+  red[t] = s;
+  __syncthreads();
+  float zj = -INFINITY;
+  if (t < K) {
+    zj = 0.f;
+    for (int l = 0; l < parts; ++l) zj += red[l * K + t];
+    zj += b[t];
+    z[n * K + t] = zj;
+  }
+  const float m = block_max(zj, sh);
+  const float lse = m + logf(block_sum(t < K ? expf(zj - m) : 0.f, sh));
+  const int lab = labels[n];
+  if (t < K) {
+    const float d = (expf(zj - lse) - (t == lab ? 1.f : 0.f)) * (1.0f / (float)N);
+    dzl[t] = d;
+    dz[n * K + t] = d;
+    if (t == lab) rowloss[n] = lse - zj;
+  }
+  if (t == 0 && (lab < 0 || lab >= K)) rowloss[n] = 0.f;
+  if (!dx) return;
+  __syncthreads();
+  for (int c = t; c < C; c += 256) {
+    float d = 0.f;
+    for (int l = 0; l < K; ++l) d = fmaf(dzl[l], Wl[c * K + l], d);
+    part[c] = d / hw;
+  }
+  __syncthreads();
+  T* out = dx + (long long)n * HW * C;
+  if (lanes > 0) {
+    spread_pixels<T, V>(part, out, HW, C, CV, lanes, accumulate);
+  } else {
+    for (int i = t; i < HW * C; i += 256) out[i] = from_f32<T>(accumulate ? to_f32<T>(out[i]) + part[i % C] : part[i % C]);
+  }
+}
+
+// The mean of the losses, in double, by one workgroup: thread sums of a stride, then a tree
+__device__ inline void mean_loss(const float* __restrict__ rowloss, float* __restrict__ loss, int N, double* sh) {
+  double s = 0.0;
+  for (int n = threadIdx.x; n < N; n += 256) s += (double)rowloss[n];
+  sh[threadIdx.x] = s;
+  __syncthreads();
+  for (int k = 128; k > 0; k >>= 1) {
+    if ((int)threadIdx.x < k) sh[threadIdx.x] += sh[threadIdx.x + k];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *loss = (float)(sh[0] / (double)N);
+}
+
+// Sums over the batch of a small head: output o = (c, j) of [pbar | 1]^T dz (row C is db), 16 lanes of samples each; the
+// last workgroup takes the loss.
+__global__ __launch_bounds__(256) void head_batch_kernel(const float* __restrict__ pbar, const float* __restrict__ dz,
+                                                         const float* __restrict__ rowloss, float* __restrict__ dW,
+                                                         float* __restrict__ db, float* __restrict__ loss, int N, int C, int K) {
+  __shared__ double shd[256];
+  if (blockIdx.x == gridDim.x - 1) {
+    mean_loss(rowloss, loss, N, shd);
+    return;
+  }
+  float* red = reinterpret_cast<float*>(shd);
+  const int ol = threadIdx.x & 15, nl = threadIdx.x >> 4, o = blockIdx.x * 16 + ol;
+  const int c = o / K, j = o - c * K;
+  float s = 0.f;
+  if (c <= C) {
+#pragma unroll 8
+    for (int n = nl; n < N; n += 16) s = fmaf(c < C ? pbar[n * C + c] : 1.f, dz[n * K + j], s);
+  }
+  red[nl * 16 + ol] = s;
+  __syncthreads();
+  if (nl == 0 && c <= C) {
+    float t = 0.f;
+#pragma unroll
+    for (int l = 0; l < 16; ++l) t += red[l * 16 + ol];
+    if (c < C) dW[o] = t;
+    else db[j] = t;
+  }
+}
+
+// ---- other heads ---------------------------------------------------------------------------------------------------
+template <typename T, int V>
+__global__ __launch_bounds__(256) void gap_kernel(const T* __restrict__ x, float* __restrict__ pbar, int HW, int C, int cvs) {
+  __shared__ float part[256 * V];
+  const int c0 = blockIdx.x * cvs * V, n = blockIdx.y;
+  const int live = min(cvs, C / V - (int)blockIdx.x * cvs);  // the last block of channels may be narrower
+  pool_pixels<T, V>(x + (long long)n * HW * C + c0, HW, C, live, 256 / live, part);
+  for (int c = threadIdx.x; c < live * V; c += 256) pbar[(long long)n * C + c0 + c] = part[c] / (float)HW;
+}
+template <typename T, int V>
+__global__ __launch_bounds__(256) void gap_vjp_kernel(const float* __restrict__ part, int splits, T* dx, int N, int HW, int C,
+                                                      int cvs, int accumulate) {
+  __shared__ float dp[256 * V];
+  const int c0 = blockIdx.x * cvs * V, n = blockIdx.y;
+  const int live = min(cvs, C / V - (int)blockIdx.x * cvs);
+  for (int c = threadIdx.x; c < live * V; c += 256) {
+    float v = 0.f;
+    for (int s = 0; s < splits; ++s) v += part[((long long)s * N + n) * C + c0 + c];
+    dp[c] = v / (float)HW;
+  }
+  __syncthreads();
+  spread_pixels<T, V>(dp, dx + (long long)n * HW * C + c0, HW, C, live, 256 / live, accumulate);
 }
 
 // part[s][m][j] = sum over the k of split s of A[m][k] * Bm(k, j), with Bm(k, j) = B[k][j] (B is [K][J]) or,
@@ -93,76 +303,66 @@ SkinnyPlan skinny_plan(int M, int J, int K) {
   return p;
 }
 
-// one block per sample: logits (the split-k partial sums, added in order, plus bias), max, sum of
-// exponentials, loss term, dz.  256 threads, fixed tree order; a thread meets the same classes in
-// every phase, so it reads back only logits it wrote itself.
+// one block per sample: logits (split-k partial sums added in order, plus the bias; or, part == nullptr, complete in z),
+// max, sum of exponentials, loss term, dz.  A thread meets the same classes in every phase, so it reads back only
+// logits it wrote itself.
 __global__ __launch_bounds__(256) void softmax_xent_kernel(const float* __restrict__ part, int splits,
                                                            const float* __restrict__ bias, float* __restrict__ z,
                                                            const int32_t* __restrict__ labels, float* __restrict__ dz,
                                                            float* __restrict__ rowloss, int N, int K) {
-  __shared__ float red[256];
+  __shared__ float sh[4];
   const int n = blockIdx.x, t = threadIdx.x;
   float* zr = z + (long long)n * K;
   float m = -INFINITY;
   for (int j = t; j < K; j += 256) {
-    float v = 0.f;
-    for (int s = 0; s < splits; ++s) v += part[((long long)s * N + n) * K + j];
-    v += bias[j];
-    zr[j] = v;
+    float v;
+    if (part) {
+      v = 0.f;
+      for (int s = 0; s < splits; ++s) v += part[((long long)s * N + n) * K + j];
+      v += bias[j];
+      zr[j] = v;
+    } else {
+      v = zr[j];
+    }
     m = fmaxf(m, v);
   }
-  red[t] = m;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (t < s) red[t] = fmaxf(red[t], red[t + s]);
-    __syncthreads();
-  }
-  m = red[0];
-  __syncthreads();
+  m = block_max(m, sh);
   float se = 0.f;
   for (int j = t; j < K; j += 256) se += expf(zr[j] - m);
-  red[t] = se;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (t < s) red[t] += red[t + s];
-    __syncthreads();
-  }
-  const float lse = m + logf(red[0]);
+  const float lse = m + logf(block_sum(se, sh));
   const int lab = labels[n];
-  const bool valid = lab >= 0 && lab < K;
   const float invN = 1.0f / (float)N;
   for (int j = t; j < K; j += 256) {
-    float p = expf(zr[j] - lse);
+    const float p = expf(zr[j] - lse);
     dz[(long long)n * K + j] = (p - (j == lab ? 1.f : 0.f)) * invN;
     if (j == lab) rowloss[n] = lse - zr[j];
   }
-  if (!valid && t == 0) rowloss[n] = 0.f;
+  if (t == 0 && (lab < 0 || lab >= K)) rowloss[n] = 0.f;
 }
 
-__global__ void mean_loss_kernel(const float* __restrict__ rowloss, float* __restrict__ loss, int N) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    double s = 0.0;
-    for (int n = 0; n < N; ++n) s += (double)rowloss[n];
-    *loss = (float)(s / (double)N);
+// db (16 classes per workgroup, 16 lanes of samples each) and, in the last workgroup, the loss
+__global__ __launch_bounds__(256) void head_bias_kernel(const float* __restrict__ dz, const float* __restrict__ rowloss,
+                                                        float* __restrict__ db, float* __restrict__ loss, int N, int K) {
+  __shared__ double shd[256];
+  if (blockIdx.x == gridDim.x - 1) {
+    mean_loss(rowloss, loss, N, shd);
+    return;
   }
-}
-
-// dx[n][hw][c] = (sum over splits of part[s][n][c]) / HW: one thread per (n, c) walks the pixels
-// (accumulate: added to what dx holds, one rounding of the sum per element)
-template <typename T>
-__global__ void gap_vjp_kernel(const float* __restrict__ part, int splits, T* dx, int N, int HW, int C, int accumulate) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N * C) return;
-  const int c = i % C, n = i / C;
-  float v = 0.f;
-  for (int s = 0; s < splits; ++s) v += part[(long long)s * N * C + i];
-  v /= (float)HW;
-  const T o = from_f32<T>(v);
-  T* p = dx + (long long)n * HW * C + c;
-  if (accumulate)
-    for (int j = 0; j < HW; ++j) p[(long long)j * C] = from_f32<T>(to_f32<T>(p[(long long)j * C]) + v);
-  else
-    for (int j = 0; j < HW; ++j) p[(long long)j * C] = o;
+  float* red = reinterpret_cast<float*>(shd);
+  const int ol = threadIdx.x & 15, nl = threadIdx.x >> 4, j = blockIdx.x * 16 + ol;
+  float s = 0.f;
+  if (j < K) {
+#pragma unroll 4
+    for (int n = nl; n < N; n += 16) s += dz[(long long)n * K + j];
+  }
+  red[nl * 16 + ol] = s;
+  __syncthreads();
+  if (nl == 0 && j < K) {
+    float t = 0.f;
+#pragma unroll
+    for (int l = 0; l < 16; ++l) t += red[l * 16 + ol];
+    db[j] = t;
+  }
 }
 
 ConvGeom dense_geom(int N, int C, int K) {
@@ -171,8 +371,17 @@ ConvGeom dense_geom(int N, int C, int K) {
   return g;
 }
 
+bool small_head(const s4tf_head_desc& d) {
+  return (long long)d.c * d.classes <= SMALL_W && d.c <= SMALL_C && d.classes <= SMALL_K && (long long)d.h * d.w * d.c <= SMALL_X;
+}
+// products on the wavefront-tile GEMM (it loads 4 adjacent channels or classes at a time)
+bool wave_head(const s4tf_head_desc& d, const void* W, const void* logits) {
+  const ConvGeom g = dense_geom(d.n, d.c, d.classes);
+  return wave_gemm_ok(PASS_FWD, g, S4TF_F32) && wave_gemm_ok(PASS_DGRAD, g, S4TF_F32) && aligned16(W) && aligned16(logits);
+}
+
 struct Layout {
-  size_t pbar, logits, dz, rowloss, part, wg, total;  // part: split-k partial sums of either skinny GEMM
+  size_t pbar, logits, dz, rowloss, part, wg, total;  // part: partial sums of either product
 };
 Layout layout(const s4tf_head_desc& d) {
   Layout l;
@@ -189,57 +398,101 @@ Layout layout(const s4tf_head_desc& d) {
   return l;
 }
 
+// KERNEL<T, V> with 16-byte accesses where the channel count allows them
+#define HEAD_LAUNCH(KERNEL, grid, ...)                                                                     \
+  do {                                                                                                     \
+    if (d.dtype == S4TF_BF16) {                                                                            \
+      typedef bf16_t T;                                                                                    \
+      if (V > 1) hipLaunchKernelGGL((KERNEL<T, 8>), grid, dim3(256), 0, st, __VA_ARGS__);                  \
+      else hipLaunchKernelGGL((KERNEL<T, 1>), grid, dim3(256), 0, st, __VA_ARGS__);                        \
+    } else {                                                                                               \
+      typedef float T;                                                                                     \
+      if (V > 1) hipLaunchKernelGGL((KERNEL<T, 4>), grid, dim3(256), 0, st, __VA_ARGS__);                  \
+      else hipLaunchKernelGGL((KERNEL<T, 1>), grid, dim3(256), 0, st, __VA_ARGS__);                        \
+    }                                                                                                      \
+  } while (0)
+
 }  // namespace
 
 size_t head_workspace(const s4tf_head_desc& d) { return layout(d).total; }
 
-int head_fwd_vjp(const s4tf_head_desc& d, const void* x, const float* W, const float* b,
-                 const int32_t* labels, float* loss, void* dx, float* dW, float* db, float* logits_out,
-                 void* ws, hipStream_t st) {
-  Layout l = layout(d);
+int head_value(const s4tf_head_desc& d, const void* x, const float* W, const float* b, const int32_t* labels, void* dx,
+               float* logits_out, void* ws, hipStream_t st) {
+  const Layout l = layout(d);
   char* base = static_cast<char*>(ws);
   float* pbar = reinterpret_cast<float*>(base + l.pbar);
   float* logits = logits_out ? logits_out : reinterpret_cast<float*>(base + l.logits);
   float* dz = reinterpret_cast<float*>(base + l.dz);
   float* rowloss = reinterpret_cast<float*>(base + l.rowloss);
   float* part = reinterpret_cast<float*>(base + l.part);
-  const int HW = d.h * d.w;
-  ConvGeom g = dense_geom(d.n, d.c, d.classes);
+  const int HW = d.h * d.w, vec = d.dtype == S4TF_BF16 ? 8 : 4;
+  const int V = d.c % vec == 0 ? vec : 1;
   int rc;
+  if (small_head(d)) {
+    ProfScope ps(PC_HEAD, st);
+    HEAD_LAUNCH(head_sample_kernel, dim3(d.n), (const T*)x, W, b, labels, pbar, logits, dz, rowloss, (T*)dx, d.n, HW, d.c, d.classes,
+                d.accumulate_dx);
+    return launch_status("head_sample");
+  }
+  // channel vectors per workgroup of the pooling kernels: 64, and narrower where that leaves the chip empty
+  int cvs = d.c / V < 64 ? d.c / V : 64;
+  while (cvs > 8 && (long long)d.n * ((d.c / V + cvs - 1) / cvs) < 256) cvs = (cvs + 1) / 2;
+  const dim3 pool_grid((unsigned)((d.c / V + cvs - 1) / cvs), (unsigned)d.n);
   {
     ProfScope ps(PC_HEAD, st);
-    int total = d.n * d.c;
-    if (d.dtype == S4TF_BF16)
-      hipLaunchKernelGGL(gap_kernel<bf16_t>, dim3((total + 255) / 256), dim3(256), 0, st, (const bf16_t*)x, pbar, d.n, HW, d.c);
-    else
-      hipLaunchKernelGGL(gap_kernel<float>, dim3((total + 255) / 256), dim3(256), 0, st, (const float*)x, pbar, d.n, HW, d.c);
+    HEAD_LAUNCH(gap_kernel, pool_grid, (const T*)x, pbar, HW, d.c, cvs);
     if ((rc = launch_status("gap")) != S4TF_OK) return rc;
   }
+  const bool waves = wave_head(d, W, logits);
+  const ConvGeom g = dense_geom(d.n, d.c, d.classes);
+  const SkinnyPlan sp = skinny_plan(d.n, d.classes, d.c), sb = skinny_plan(d.n, d.c, d.classes);
   {
     ProfScope ps(PC_HEAD, st);
-    const SkinnyPlan sp = skinny_plan(d.n, d.classes, d.c);
-    hipLaunchKernelGGL(skinny_gemm_kernel<false>, sp.grid, dim3(256), 0, st, pbar, W, part, d.n, d.classes, d.c, sp.kper);
-    if ((rc = launch_status("head logits")) != S4TF_OK) return rc;
-    hipLaunchKernelGGL(softmax_xent_kernel, dim3(d.n), dim3(256), 0, st, part, sp.splits, b, logits, labels, dz, rowloss, d.n, d.classes);
+    if (waves) {
+      if ((rc = wave_gemm_fwd(g, pbar, W, b, S4TF_ACT_NONE, logits, nullptr, nullptr, st)) != S4TF_OK) return rc;
+    } else {
+      hipLaunchKernelGGL(skinny_gemm_kernel<false>, sp.grid, dim3(256), 0, st, pbar, W, part, d.n, d.classes, d.c, sp.kper);
+      if ((rc = launch_status("head logits")) != S4TF_OK) return rc;
+    }
+    hipLaunchKernelGGL(softmax_xent_kernel, dim3(d.n), dim3(256), 0, st, waves ? nullptr : part, sp.splits, b, logits, labels, dz,
+                       rowloss, d.n, d.classes);
     if ((rc = launch_status("softmax_xent")) != S4TF_OK) return rc;
-    hipLaunchKernelGGL(mean_loss_kernel, dim3(1), dim3(64), 0, st, rowloss, loss, d.n);
-    if ((rc = launch_status("mean_loss")) != S4TF_OK) return rc;
   }
-  if ((rc = igemm_wgrad(g, S4TF_F32, pbar, dz, dW, base + l.wg, l.total - l.wg, st)) != S4TF_OK) return rc;
-  if ((rc = colsum(S4TF_F32, dz, (size_t)d.n, d.classes, db, st)) != S4TF_OK) return rc;
-  if (dx) {
-    ProfScope ps(PC_HEAD, st);
-    const SkinnyPlan sp = skinny_plan(d.n, d.c, d.classes);  // dpbar[n][c] = sum_j dz[n][j] W[c][j]
-    hipLaunchKernelGGL(skinny_gemm_kernel<true>, sp.grid, dim3(256), 0, st, dz, W, part, d.n, d.c, d.classes, sp.kper);
+  if (!dx) return S4TF_OK;
+  ProfScope ps(PC_HEAD, st);  // dpbar[n][c] = sum_j dz[n][j] W[c][j]
+  if (waves) {
+    if ((rc = wave_gemm_dgrad(g, dz, W, part, 0, st)) != S4TF_OK) return rc;
+  } else {
+    hipLaunchKernelGGL(skinny_gemm_kernel<true>, sb.grid, dim3(256), 0, st, dz, W, part, d.n, d.c, d.classes, sb.kper);
     if ((rc = launch_status("head dpbar")) != S4TF_OK) return rc;
-    const unsigned blocks = (unsigned)(((long long)d.n * d.c + 255) / 256);
-    if (d.dtype == S4TF_BF16)
-      hipLaunchKernelGGL(gap_vjp_kernel<bf16_t>, dim3(blocks), dim3(256), 0, st, part, sp.splits, (bf16_t*)dx, d.n, HW, d.c, d.accumulate_dx);
-    else
-      hipLaunchKernelGGL(gap_vjp_kernel<float>, dim3(blocks), dim3(256), 0, st, part, sp.splits, (float*)dx, d.n, HW, d.c, d.accumulate_dx);
-    if ((rc = launch_status("gap_vjp")) != S4TF_OK) return rc;
   }
-  return S4TF_OK;
+  HEAD_LAUNCH(gap_vjp_kernel, pool_grid, part, waves ? 1 : sb.splits, (T*)dx, d.n, HW, d.c, cvs, d.accumulate_dx);
+  return launch_status("gap_vjp");
+}
+
+int head_params(const s4tf_head_desc& d, float* loss, float* dW, float* db, void* ws, hipStream_t st) {
+  const Layout l = layout(d);
+  char* base = static_cast<char*>(ws);
+  const float* pbar = reinterpret_cast<const float*>(base + l.pbar);
+  const float* dz = reinterpret_cast<const float*>(base + l.dz);
+  const float* rowloss = reinterpret_cast<const float*>(base + l.rowloss);
+  if (small_head(d)) {
+    ProfScope ps(PC_HEAD, st);
+    hipLaunchKernelGGL(head_batch_kernel, dim3(((d.c + 1) * d.classes + 15) / 16 + 1), dim3(256), 0, st, pbar, dz, rowloss, dW, db,
+                       loss, d.n, d.c, d.classes);
+    return launch_status("head_batch");
+  }
+  int rc = igemm_wgrad(dense_geom(d.n, d.c, d.classes), S4TF_F32, pbar, dz, dW, base + l.wg, l.total - l.wg, st);
+  if (rc != S4TF_OK) return rc;
+  ProfScope ps(PC_HEAD, st);
+  hipLaunchKernelGGL(head_bias_kernel, dim3((d.classes + 15) / 16 + 1), dim3(256), 0, st, dz, rowloss, db, loss, d.n, d.classes);
+  return launch_status("head_bias");
+}
+
+int head_fwd_vjp(const s4tf_head_desc& d, const void* x, const float* W, const float* b, const int32_t* labels, float* loss,
+                 void* dx, float* dW, float* db, float* logits_out, void* ws, hipStream_t st) {
+  const int rc = head_value(d, x, W, b, labels, dx, logits_out, ws, st);
+  return rc != S4TF_OK ? rc : head_params(d, loss, dW, db, ws, st);
 }
 
 }  // namespace s4tf

@@ -171,11 +171,14 @@ bool pool_saves_positions(const s4tf_pool_desc& d);
 int pool_fwd(const s4tf_pool_desc& d, const void* x, void* y, hipStream_t st, unsigned char* idx = nullptr);
 int pool_vjp(const s4tf_pool_desc& d, const void* x, const void* dy, void* dx, hipStream_t st, const unsigned char* idx = nullptr);
 
-// head
+// head.  head_value: logits, cotangents of the logits (kept in ws) and dx; head_params: loss, dW and db from what it left in ws
+// (possibly on another stream, ordered behind it); head_fwd_vjp: both.
 size_t head_workspace(const s4tf_head_desc& d);
-int head_fwd_vjp(const s4tf_head_desc& d, const void* x, const float* W, const float* b,
-                 const int32_t* labels, float* loss, void* dx, float* dW, float* db, float* logits,
-                 void* ws, hipStream_t st);
+int head_value(const s4tf_head_desc& d, const void* x, const float* W, const float* b, const int32_t* labels, void* dx,
+               float* logits, void* ws, hipStream_t st);
+int head_params(const s4tf_head_desc& d, float* loss, float* dW, float* db, void* ws, hipStream_t st);
+int head_fwd_vjp(const s4tf_head_desc& d, const void* x, const float* W, const float* b, const int32_t* labels, float* loss,
+                 void* dx, float* dW, float* db, float* logits, void* ws, hipStream_t st);
 
 // indexing: y[j,:] = x[index[j],:] and its in-place pullback dx[index[j],:] += dy[j,:] (in order of j)
 int gather_rows_fwd(const s4tf_gather_desc& d, const void* x, const int32_t* index, void* y, hipStream_t st);

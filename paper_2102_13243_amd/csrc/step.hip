@@ -91,6 +91,7 @@ struct NetPlan {
   std::vector<size_t> xpad_off, wpad_off, dwpad_off;
   size_t param_count;
   size_t scratch_off, scratch_bytes, total_bytes;
+  size_t head_off, head_bytes;          // what the head keeps for its parameters' gradients, which run on the second stream
   size_t wscratch_off, wscratch_bytes;  // scratch of the filter-gradient kernels, which run on a stream of their own
   // Side branches: a convolution + BatchNorm pair whose only use is as the residual input of a later
   // BatchNorm (the projection shortcut of a residual block), while other ops lie between the pair and
@@ -233,8 +234,7 @@ int plan_net(const s4tf_net_desc* net, NetPlan& pl) {
         if (rc != S4TF_OK) return rc;
         add_param(i, 0, (size_t)in.c * op.k);
         add_param(i, 1, (size_t)op.k);
-        size_t ws = head_workspace(d);
-        if (ws > scratch) scratch = ws;
+        pl.head_bytes = head_workspace(d);
         out.h = 1; out.w = 1; out.c = op.k;
         break;
       }
@@ -301,7 +301,8 @@ int plan_net(const s4tf_net_desc* net, NetPlan& pl) {
   pl.wscratch_off = pl.scratch_off + pl.scratch_bytes;
   pl.wscratch_bytes = align_up(wscratch, 256);
   pl.sscratch_off = pl.wscratch_off + pl.wscratch_bytes;
-  pl.total_bytes = pl.sscratch_off + pl.scratch_bytes;
+  pl.head_off = pl.sscratch_off + pl.scratch_bytes;
+  pl.total_bytes = pl.head_off + align_up(pl.head_bytes, 256);
   // side branches
   pl.branch_of.assign(nops, -1);
   pl.start_after.assign(nops, -1);
@@ -350,7 +351,8 @@ int plan_net(const s4tf_net_desc* net, NetPlan& pl) {
 // ---- the schedule -------------------------------------------------------------------------------------------
 enum CmdKind : uint8_t {
   K_FORK, K_JOIN, K_SIDE_DONE, K_WAIT_SIDE,        // stream operations (a: event slot)
-  K_CONV_FWD, K_BN_FWD, K_POOL_FWD, K_HEAD,        // forward (conv: a = 1 when it emits statistics partial sums)
+  K_CONV_FWD, K_BN_FWD, K_POOL_FWD, K_HEAD, K_HEAD_PARAMS,  // forward (conv: a = 1 when it emits statistics partial
+                                                   //  sums; head: b = 1 when its parameter gradients follow at once)
   K_ACT_VJP, K_DGRAD, K_PARAM_GRADS, K_BN_VJP,     // pullbacks (dgrad: a = accumulate, b = BatchNorm whose residual
   K_POOL_VJP, K_SGD                                //  cotangent it adds or -1; bn: a = accumulate into dres, b = 1 when
 };                                                 //  dres is left to that dgrad; pool: a = accumulate; sgd: a = part)
@@ -392,7 +394,12 @@ int record_schedule(s4tf_net& N) {
   // side -> main dependencies: the event slot a side branch's output (forward) or a tensor's cotangent
   // (backward) is ready at; the main stream waits for it where it first touches that data
   int back_next = 0;
-  auto fork = [&]() { if (!one_stream) emit(K_FORK, false, false, -1); };
+  bool head_params_due = false;  // the head's parameter gradients go along with the next hand-over to the second stream
+  auto fork = [&]() {
+    if (!one_stream) emit(K_FORK, false, false, -1);
+    if (head_params_due) emit(K_HEAD_PARAMS, true, false, nops - 1);
+    head_params_due = false;
+  };
   auto side_done = [&](int& slot) {
     if (one_stream) return;
     slot = back_next++ % 8;
@@ -441,8 +448,9 @@ int record_schedule(s4tf_net& N) {
   std::vector<char> written(nops + 1, 0);
   {
     const int src = resolve(net->ops[nops - 1].in);
-    emit(K_HEAD, false, false, nops - 1, src);
+    emit(K_HEAD, false, false, nops - 1, src, one_stream ? 1 : 0);
     written[src] = 1;
+    head_params_due = !one_stream;
   }
   // ---- pullbacks in reverse op order ----
   // Ops of a side branch run on the side stream (after the op that feeds them their cotangent, which
@@ -546,6 +554,7 @@ int record_schedule(s4tf_net& N) {
     }
   }
   flush_pending();
+  if (head_params_due) fork();
   for (int t = 1; t < nops; ++t)
     if (deferred[t] >= 0) return fail(S4TF_ERR_UNSUPPORTED, "residual cotangent of tensor %d left without a convolution to add it", t);
   // ---- optimizer: one launch over the whole arena, once the side stream's gradients are in ----
@@ -752,9 +761,17 @@ int run_step(const s4tf_net& N, s4tf_params* params, const s4tf_batch* batch, fl
         const TensorPlan& in = pl.t[op.in];
         s4tf_head_desc d = {in.n, in.h, in.w, in.c, op.k, dt};
         void* dx = c.a == 0 ? nullptr : grad_ptr(c.a);
-        CHECK(head_fwd_vjp(d, act_ptr(op.in), params->master + pl.poff[2 * i], params->master + pl.poff[2 * i + 1],
-                           batch->labels, batch->loss, dx, params->grad + pl.poff[2 * i], params->grad + pl.poff[2 * i + 1],
-                           nullptr, scr, s));
+        CHECK(head_value(d, act_ptr(op.in), params->master + pl.poff[2 * i], params->master + pl.poff[2 * i + 1], batch->labels, dx,
+                         nullptr, ws + pl.head_off, s));
+        if (c.b == 1)
+          CHECK(head_params(d, batch->loss, params->grad + pl.poff[2 * i], params->grad + pl.poff[2 * i + 1], ws + pl.head_off, s));
+        break;
+      }
+      case K_HEAD_PARAMS: {
+        const s4tf_op& op = net->ops[i];
+        const TensorPlan& in = pl.t[op.in];
+        s4tf_head_desc d = {in.n, in.h, in.w, in.c, op.k, dt};
+        CHECK(head_params(d, batch->loss, params->grad + pl.poff[2 * i], params->grad + pl.poff[2 * i + 1], ws + pl.head_off, s));
         break;
       }
       case K_ACT_VJP:

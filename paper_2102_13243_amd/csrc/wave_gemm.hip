@@ -8,10 +8,10 @@
 // no concern at that tile size.  What bounds these layers (a few thousand such wavefront tiles, 9 to 80 k-steps each) is
 // latency: with operand tiles shared by a workgroup, every k-tile paid a memory latency and two barriers.  Here a
 // wavefront owns a ring of STAGES LDS slots, fills it with 16-byte direct loads (buffer_load ... lds) and waits only on
-// its own vmcnt: no barrier in the loop, and wavefronts of a SIMD drift apart and cover each other.  (Fragments loaded
-// from global memory straight into registers were measured too: adjacent lanes then lie in different rows,
-// four cache accesses per 64 bytes, and the address unit becomes the bound: 53 us where this takes 36, 16x28x28
-// 128 -> 128 3x3.)
+// its own vmcnt: no barrier in the loop, and wavefronts of a SIMD drift apart and cover each other.  Forward, batch 32,
+// staged per workgroup / here: 14x14 576 -> 96 22.3 / 13.1 us, 7x7 960 -> 160 18.2 / 9.8; batch 5, 5x5 960 -> 160
+// 17.7 / 6.7.  (Fragments loaded from global memory straight into registers were measured too: adjacent lanes then lie
+// in different rows, four cache accesses per 64 bytes, and the address unit becomes the bound: 15.4, 12.7 and 11.3.)
 //
 // k-step: 16 values of k; MFMA e takes k = 4*(l/16) + e from lane l, so a lane's four values are adjacent.
 //   * operands contiguous along k (A of forward and dgrad: rows of pixels; B of dgrad: filter rows) lie in LDS as

@@ -487,6 +487,15 @@ def test_head_seeded_random_shapes(shape, bf16):
 
 
 @pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
+@pytest.mark.parametrize("shape", [
+    (2, 3, 3, 512, 16), (1, 2, 2, 32, 256), (3, 1, 2, 1023, 8), (17, 5, 5, 12, 3),    # at the limits of the small head
+    (2, 3, 3, 513, 16), (3, 2, 2, 300, 101), (2, 4, 4, 1001, 9), (1, 33, 32, 64, 4),  # just beyond it, ragged and not
+    (70, 2, 2, 136, 132)], ids=lambda s: "x".join(map(str, s)))
+def test_head_edges(shape, bf16):
+    test_head(shape, bf16)
+
+
+@pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
 @pytest.mark.parametrize("shape", [(8, 16, 16, 16, 10), (128, 1, 1, 84, 10), (6, 7, 7, 256, 1000), (3, 2, 3, 20, 7)],
                          ids=lambda s: "x".join(map(str, s)))
 def test_head(shape, bf16):
