@@ -115,26 +115,42 @@ __device__ inline void block_lane_sum(A (&v)[NV], A* red, int cvb, int cvl) {
   block_lane_sum<A, NV>(v, red, cvb, cvb, cvl);
 }
 
-// Walk the pixels first, first+step, ... < p1 of a chunk, UNROLL at a time: `load(m, slot)` issues
+// Walk the pixels first, first+step, ... < p1 of a chunk, U at a time: `load(m, slot)` issues
 // the loads of pixel m into slot, `use(m, slot)` consumes them.
-template <typename Load, typename Use>
+template <int U = UNROLL, typename Load, typename Use>
 __device__ inline void walk_pixels(long long first, long long p1, long long step, Load load, Use use) {
   long long m = first;
-  for (; m + (UNROLL - 1) * step < p1; m += UNROLL * step) {
+  for (; m + (U - 1) * step < p1; m += U * step) {
 #pragma unroll
-    for (int u = 0; u < UNROLL; ++u) load(m + u * step, u);
+    for (int u = 0; u < U; ++u) load(m + u * step, u);
 #pragma unroll
-    for (int u = 0; u < UNROLL; ++u) use(m + u * step, u);
+    for (int u = 0; u < U; ++u) use(m + u * step, u);
   }
-  // the last, partial round (at most UNROLL - 1 pixels) the same way: all its loads first (a slot past the end
+  // the last, partial round (at most U - 1 pixels) the same way: all its loads first (a slot past the end
   // re-loads pixel m and is not used), so that it costs one memory latency and not one per pixel
   if (m < p1) {
 #pragma unroll
-    for (int u = 0; u < UNROLL - 1; ++u) load(m + u * step < p1 ? m + u * step : m, u);
+    for (int u = 0; u < U - 1; ++u) load(m + u * step < p1 ? m + u * step : m, u);
 #pragma unroll
-    for (int u = 0; u < UNROLL - 1; ++u)
+    for (int u = 0; u < U - 1; ++u)
       if (m + u * step < p1) use(m + u * step, u);
   }
+}
+
+// The same in two parts, for kernels that have something else to wait for before they can use a pixel: the loads of the
+// first round, and later everything else.
+template <int U, typename Load>
+__device__ inline void load_ahead(long long first, long long p1, long long step, Load load) {
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (first + u * step < p1) load(first + u * step, u);
+}
+template <int U, typename Load, typename Use>
+__device__ inline void walk_loaded(long long first, long long p1, long long step, Load load, Use use) {
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (first + u * step < p1) use(first + u * step, u);
+  walk_pixels<U>(first + U * step, p1, step, load, use);
 }
 
 template <typename T, int V>
@@ -548,6 +564,465 @@ template <typename T, int V> __global__ __launch_bounds__(256) void bn_vjp_apply
                                              cvb, per, act, reinterpret_cast<const unsigned char*>(y));
 }
 
+// ---- layers small enough for the sums to be finished inside the kernel that uses them -----------------------------
+// A launch costs a dependent chain 4 to 6 us here (the kernel's own latencies and 1.5 us between kernels), as much as
+// reading a 10 MB tensor.  Where the table of partial sums behind one block's channels is small, the apply kernels
+// therefore take it as it is: every block adds up the table for its own channels (from L2) while its first pixels are
+// on their way, and the finalize launch is gone.  Blocks of 1024 threads, about one per CU: each repeats that prologue.
+// Limits by measurement (step times of five networks): a table of 128 KB per block costs the forward pass less than a
+// launch; the pullback's, in double, pays up to 40 KB; bf16 pullbacks beyond 3 MB are bound by vector arithmetic and
+// keep the kernels with more blocks (ResNet-50 at batch 64: 6.88 ms, with a limit of 32 MB 6.97).
+// MobileNetV2 at batch 5 1.81 -> 1.64 ms (with the kernels for up to 512 pixels below), at batch 32 4.17 -> 4.00,
+// ResNet-50 at batch 13 and 176x176 2.91 -> 2.74, ResNet-56 3.18 -> 3.11.
+constexpr int WIDE = 1024;
+constexpr size_t MERGE_TABLE_BYTES = 128 << 10, MERGE_VJP_TABLE_BYTES = 40000;
+constexpr size_t merge_vjp_tensor_bytes(int dtype) { return dtype == S4TF_BF16 ? (size_t)3 << 20 : (size_t)32 << 20; }
+
+// Channel blocks of 64 or 128 bytes a pixel, pixel chunks so that there is about one block per CU
+Plan make_wide_plan(size_t M, int C, int dtype, int target_blocks) {
+  Plan p;
+  p.V = dtype == S4TF_BF16 ? 8 : 4;
+  const int CV = C / p.V;
+  p.cvb = 4;  // 64 bytes; 128 where a tensor is big enough for half lines to cost bandwidth, or has many channels
+  if (CV >= 8 && (M * (size_t)C * (16 / p.V) > (1u << 20) || CV > 256)) p.cvb = 8;
+  p.cblocks = (CV + p.cvb - 1) / p.cvb;
+  p.pl = WIDE / p.cvb;
+  long long want = target_blocks / p.cblocks;
+  if (want < 1) want = 1;
+  long long per = ((long long)M + want - 1) / want;
+  if (per < p.pl) per = p.pl;
+  p.per = per;
+  p.chunks = (int)(((long long)M + per - 1) / per);
+  return p;
+}
+
+// mean and 1/std of the cb <= 64 channels from c0 on, out of a convolution's table (see bn_stats_from_runs_kernel): 16 to
+// 64 lanes per channel, in double
+__device__ inline void stats_of_block(const float* __restrict__ part, int runs, int rows, long long M, int C, float eps, int c0,
+                                      int cb, float* mu, float* is) {
+  const int lpc = cb <= 16 ? 64 : cb <= 32 ? 32 : 16;  // WIDE / lpc channels at least cb
+  const int ch = threadIdx.x / lpc, l = threadIdx.x % lpc, c = c0 + ch;
+  double S = 0.0, Q = 0.0, W = 0.0;
+  const bool live = ch < cb && c < C;
+  if (live) {
+    const double inv_rows = 1.0 / (double)rows, inv_last = 1.0 / (double)(M - (long long)(runs - 1) * rows);
+    const float* __restrict__ srow = part + (long long)c * runs;
+    const float* __restrict__ qrow = part + ((long long)C + c) * runs;
+#pragma unroll 8
+    for (int i = l; i < runs; i += lpc) {
+      const double sv = (double)srow[i];
+      S += sv;
+      Q += (double)qrow[i];
+      W += sv * sv * (i == runs - 1 ? inv_last : inv_rows);
+    }
+  }
+  for (int off = 1; off < lpc; off <<= 1) {
+    S += __shfl_xor(S, off, 64);
+    Q += __shfl_xor(Q, off, 64);
+    W += __shfl_xor(W, off, 64);
+  }
+  if (live && l == 0) {
+    double var = (Q + W - S * S / (double)M) / (double)M;
+    if (var < 0.0) var = 0.0;
+    mu[ch] = (float)(S / (double)M);
+    is[ch] = (float)(1.0 / sqrt(var + (double)eps));
+  }
+  __syncthreads();
+}
+
+template <typename T, int V>
+__global__ __launch_bounds__(WIDE) void bn_apply_runs_kernel(const T* __restrict__ x, const T* __restrict__ res,
+                                                             const float* __restrict__ gamma, const float* __restrict__ beta,
+                                                             const float* __restrict__ part, int runs, int rows, float eps,
+                                                             float* __restrict__ mean, float* __restrict__ invstd,
+                                                             T* __restrict__ y, unsigned char* __restrict__ bits, long long M,
+                                                             int C, int cvb, long long per, int act) {
+  __shared__ float mul[64], isl[64];
+  const int CV = C / V, pl_count = WIDE / cvb, cvl = threadIdx.x % cvb, pl = threadIdx.x / cvb;
+  const int cv = blockIdx.x * cvb + cvl, cb = min(cvb, CV - (int)blockIdx.x * cvb) * V, c0 = blockIdx.x * cvb * V;
+  const bool live = cv < CV;
+  const int c = live ? cv * V : 0;
+  const long long p0 = (long long)blockIdx.y * per, p1 = !live ? 0 : p0 + per < M ? p0 + per : M;
+  constexpr int U = 4;
+  Pack<T, V> xv[U], rv[U];
+  auto load = [&](long long m, int u) {
+    xv[u] = ldp<T, V>(x + m * C + c);
+    if (res) rv[u] = ldp<T, V>(res + m * C + c);
+  };
+  load_ahead<U>(p0 + pl, p1, pl_count, load);  // on their way while the block adds up its channels' sums
+  stats_of_block(part, runs, rows, M, C, eps, c0, cb, mul, isl);
+  if (blockIdx.y == 0 && (int)threadIdx.x < cb) {
+    mean[c0 + threadIdx.x] = mul[threadIdx.x];
+    invstd[c0 + threadIdx.x] = isl[threadIdx.x];
+  }
+  if (!live) return;
+  const float mhi = remask_hi<T>(act);
+  float mu[V], sc[V], be[V];
+#pragma unroll
+  for (int e = 0; e < V; ++e) {
+    mu[e] = mul[cvl * V + e];
+    sc[e] = gamma[c + e] * isl[cvl * V + e];
+    be[e] = beta[c + e];
+  }
+  const float act_lo = act == S4TF_ACT_NONE ? -__builtin_inff() : 0.f;
+  const float act_hi = act == S4TF_ACT_RELU6 ? 6.f : __builtin_inff();
+  walk_loaded<U>(p0 + pl, p1, pl_count, load,
+              [&](long long m, int u) {
+                float o[V];
+                unsigned b = 0;
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                  float z = bn_z(xv[u].get(e), mu[e], sc[e], be[e]);
+                  if (res) z += rv[u].get(e);
+                  o[e] = fminf(fmaxf(z, act_lo), act_hi);
+                  b |= (z > 0.f && z < mhi) ? (1u << e) : 0u;
+                }
+                stp<T, V>(y + m * C + c, pack_of<T, V>(o));
+                if (bits) bits[m * CV + cv] = (unsigned char)b;
+              });
+}
+
+// dz = dy * act'(y) of one channel vector and pixel.  MODE: where act' comes from.
+enum { MASK_Y = 0, MASK_Z = 1, MASK_BITS = 2 };  // the stored output, z rebuilt from x, the forward pass's bits
+template <typename T, int V, int MODE>
+__device__ __forceinline__ float bn_dz(const Pack<T, V>& dv, const Pack<T, V>& yv, unsigned bv, float z, int e, int act, float zhi,
+                                       float yhi) {
+  const float dz = dv.get(e);
+  if (MODE == MASK_BITS) return ((bv >> e) & 1) ? dz : 0.f;
+  if (MODE == MASK_Z) return (z > 0.f && z < zhi) ? dz : 0.f;
+  if (act == S4TF_ACT_NONE) return dz;
+  const float yy = yv.get(e);
+  return (yy > 0.f && yy < yhi) ? dz : 0.f;
+}
+
+// Adds 2*V sums per channel vector over the pixel lanes of a WIDE block, in double from the wavefronts on.  Thread
+// (pixel lane, cvl) -> LDS out[2][cvb*V]: [0] sum dz, [1] sum dz*xhat.  red: 2 * 16 * cvb * V doubles.
+template <int V>
+__device__ inline void wide_sums(float (&grp)[2 * V], int cvb, int cvl, double* red, double* out) {
+  for (int off = cvb; off < 64; off <<= 1) {
+#pragma unroll
+    for (int e = 0; e < 2 * V; ++e) grp[e] += __shfl_xor(grp[e], off, 64);
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, cb = cvb * V;
+  if (lane < cvb) {
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      red[(wave * 2) * cb + cvl * V + e] = (double)grp[e];
+      red[(wave * 2 + 1) * cb + cvl * V + e] = (double)grp[V + e];
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < 2 * cb; i += WIDE) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < WIDE / 64; ++w) t += red[w * 2 * cb + i];
+    out[i] = t;
+  }
+  __syncthreads();
+}
+
+template <typename T, int V, int MODE>
+__global__ __launch_bounds__(WIDE) void bn_vjp_reduce_wide_kernel(const T* __restrict__ x, const T* __restrict__ y,
+                                                                  const T* __restrict__ dy, const float* __restrict__ mean,
+                                                                  const float* __restrict__ invstd, const float* __restrict__ gamma,
+                                                                  const float* __restrict__ beta, double* __restrict__ part,
+                                                                  long long M, int C, int cvb, long long per, int act) {
+  __shared__ double red[(WIDE / 64) * 2 * 64], sums[2 * 64];
+  const unsigned char* __restrict__ bits = reinterpret_cast<const unsigned char*>(y);
+  const int CV = C / V, pl_count = WIDE / cvb, cvl = threadIdx.x % cvb, pl = threadIdx.x / cvb;
+  const int cv = blockIdx.x * cvb + cvl;
+  const bool live = cv < CV;
+  const int c = live ? cv * V : 0;
+  const float mhi = remask_hi<T>(act), yhi = act == S4TF_ACT_RELU6 ? 6.f : __builtin_inff();
+  float grp[2 * V], mu[V], is[V], sc[V], be[V];
+#pragma unroll
+  for (int e = 0; e < V; ++e) {
+    grp[e] = grp[V + e] = 0.f;
+    mu[e] = mean[c + e];
+    is[e] = invstd[c + e];
+    sc[e] = MODE == MASK_Z ? gamma[c + e] * is[e] : 0.f;
+    be[e] = MODE == MASK_Z ? beta[c + e] : 0.f;
+  }
+  const long long p0 = (long long)blockIdx.y * per, p1 = p0 + per < M ? p0 + per : M;
+  if (live) {
+    Pack<T, V> xv[UNROLL], dv[UNROLL], yv[UNROLL];
+    unsigned bv[UNROLL];
+    walk_pixels(p0 + pl, p1, pl_count,
+                [&](long long m, int u) {
+                  xv[u] = ldp<T, V>(x + m * C + c);
+                  dv[u] = ldp<T, V>(dy + m * C + c);
+                  if (MODE == MASK_BITS) bv[u] = bits[m * CV + cv];
+                  else if (MODE == MASK_Y && act != S4TF_ACT_NONE) yv[u] = ldp<T, V>(y + m * C + c);
+                },
+                [&](long long, int u) {
+#pragma unroll
+                  for (int e = 0; e < V; ++e) {
+                    const float xc = xv[u].get(e) - mu[e];
+                    const float dz = bn_dz<T, V, MODE>(dv[u], yv[u], bv[u], fmaf(xc, sc[e], be[e]), e, act, mhi, yhi);
+                    grp[e] += dz;
+                    grp[V + e] += dz * (xc * is[e]);
+                  }
+                });
+  }
+  wide_sums<V>(grp, cvb, cvl, red, sums);
+  const int cb = cvb * V, c0 = blockIdx.x * cb;
+  double* dst = part + (long long)blockIdx.y * 2 * C;
+  for (int i = threadIdx.x; i < 2 * cb; i += WIDE) {
+    const int w = i / cb, k = i - w * cb;
+    if (c0 + k < C) dst[w * C + c0 + k] = sums[i];
+  }
+}
+
+// the chunks' sums of this block's channels, added in a fixed order: thread (chunk lane, channel), wavefront, then LDS
+__device__ inline void sums_of_block(const double* __restrict__ part, int chunks, int C, int c0, int cb, double* red, double* out) {
+  const int cbp = cb <= 16 ? 16 : cb <= 32 ? 32 : 64;  // a power of two that divides a wavefront
+  const int k = threadIdx.x % cbp, zl = threadIdx.x / cbp, lanes = WIDE / cbp;
+  double a = 0.0, b = 0.0;
+  if (k < cb && c0 + k < C) {
+#pragma unroll 4
+    for (int z = zl; z < chunks; z += lanes) {
+      a += part[(long long)z * 2 * C + c0 + k];
+      b += part[((long long)z * 2 + 1) * C + c0 + k];
+    }
+  }
+  for (int off = cbp; off < 64; off <<= 1) {
+    a += __shfl_xor(a, off, 64);
+    b += __shfl_xor(b, off, 64);
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (lane < cbp) {
+    red[wave * 2 * 64 + k] = a;
+    red[(wave * 2 + 1) * 64 + k] = b;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < 2 * cb; i += WIDE) {
+    const int w = i / cb, kk = i - w * cb;
+    double t = 0.0;
+#pragma unroll
+    for (int v = 0; v < WIDE / 64; ++v) t += red[(v * 2 + w) * 64 + kk];
+    out[i] = t;
+  }
+  __syncthreads();
+}
+
+// dx = gs*dz - (x - mu)*a2 - a0 (see bn_vjp_apply_body), dres (+)= dz
+template <typename T, int V> struct VjpCoef {
+  float mu[V], gs[V], a0[V], a2[V], be[V];
+  __device__ void init(const float* mean, const float* invstd, const float* gamma, const float* beta, const double* sums, int cb,
+                       int cvl, int c, float invM, bool remask) {
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      const float is = invstd[c + e];
+      mu[e] = mean[c + e];
+      be[e] = remask ? beta[c + e] : 0.f;
+      gs[e] = gamma[c + e] * is;
+      a0[e] = gs[e] * ((float)sums[cvl * V + e] * invM);
+      a2[e] = gs[e] * (is * ((float)sums[cb + cvl * V + e] * invM));
+    }
+  }
+};
+
+template <typename T, int V, int MODE>
+__global__ __launch_bounds__(WIDE) void bn_vjp_apply_wide_kernel(const T* __restrict__ x, const T* __restrict__ y,
+                                                                 const T* __restrict__ dy, const float* __restrict__ gamma,
+                                                                 const float* __restrict__ mean, const float* __restrict__ invstd,
+                                                                 const float* __restrict__ beta, const double* __restrict__ part,
+                                                                 int chunks, float* __restrict__ dgamma, float* __restrict__ dbeta,
+                                                                 T* dx, T* dres, int acc_dx, int acc_dres, long long M, int C,
+                                                                 int cvb, long long per, int act) {
+  __shared__ double red[(WIDE / 64) * 2 * 64], sums[2 * 64];
+  const unsigned char* __restrict__ bits = reinterpret_cast<const unsigned char*>(y);
+  const int CV = C / V, pl_count = WIDE / cvb, cvl = threadIdx.x % cvb, pl = threadIdx.x / cvb;
+  const int cv = blockIdx.x * cvb + cvl, cb = cvb * V, c0 = blockIdx.x * cb;
+  const bool live = cv < CV;
+  const int c = live ? cv * V : 0;
+  const long long p0 = (long long)blockIdx.y * per, p1 = !live ? 0 : p0 + per < M ? p0 + per : M;
+  constexpr int U = 2;
+  Pack<T, V> xv[U], dv[U], yv[U], ov[U], av[U];
+  unsigned bv[U];
+  auto load = [&](long long m, int u) {
+    xv[u] = ldp<T, V>(x + m * C + c);
+    dv[u] = ldp<T, V>(dy + m * C + c);
+    if (MODE == MASK_BITS) bv[u] = bits[m * CV + cv];
+    else if (MODE == MASK_Y && act != S4TF_ACT_NONE) yv[u] = ldp<T, V>(y + m * C + c);
+    if (dres && acc_dres) ov[u] = ldp<T, V>(dres + m * C + c);
+    if (acc_dx) av[u] = ldp<T, V>(dx + m * C + c);
+  };
+  load_ahead<U>(p0 + pl, p1, pl_count, load);  // on their way while the block adds up its channels' sums
+  sums_of_block(part, chunks, C, c0, cb, red, sums);
+  if (blockIdx.y == 0 && (int)threadIdx.x < cb && c0 + (int)threadIdx.x < C) {
+    dbeta[c0 + threadIdx.x] = (float)sums[threadIdx.x];
+    dgamma[c0 + threadIdx.x] = (float)sums[cb + threadIdx.x];
+  }
+  if (!live) return;
+  const float mhi = remask_hi<T>(act), yhi = act == S4TF_ACT_RELU6 ? 6.f : __builtin_inff();
+  VjpCoef<T, V> k;
+  k.init(mean, invstd, gamma, beta, sums, cb, cvl, c, 1.0f / (float)M, MODE == MASK_Z);
+  walk_loaded<U>(p0 + pl, p1, pl_count, load,
+              [&](long long m, int u) {
+                float o[V], r[V];
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                  const float xc = xv[u].get(e) - k.mu[e];
+                  const float dz = bn_dz<T, V, MODE>(dv[u], yv[u], bv[u], fmaf(xc, k.gs[e], k.be[e]), e, act, mhi, yhi);
+                  o[e] = fmaf(k.gs[e], dz, -fmaf(xc, k.a2[e], k.a0[e]));
+                  if (acc_dx) o[e] += av[u].get(e);
+                  r[e] = (dres && acc_dres) ? ov[u].get(e) + dz : dz;
+                }
+                stp<T, V>(dx + m * C + c, pack_of<T, V>(o));
+                if (dres) stp<T, V>(dres + m * C + c, pack_of<T, V>(r));
+              });
+}
+
+// The whole pullback of a BatchNorm over at most HOLD * WIDE / 4 pixels in one launch: a block owns four channel vectors
+// (64 bytes a pixel) over all pixels, a thread keeps its x and dz in registers between the sums and dx.  (With 8 pixels a
+// thread, 2048 in all, the few blocks of a layer of few channels took 13 to 18 us, more than the separate kernels.)
+constexpr int HOLD = 2;
+constexpr size_t HOLD_PIXELS = (size_t)HOLD * WIDE / 4;
+template <typename T, int V, int MODE>
+__global__ __launch_bounds__(WIDE) void bn_vjp_whole_kernel(const T* __restrict__ x, const T* __restrict__ y,
+                                                            const T* __restrict__ dy, const float* __restrict__ gamma,
+                                                            const float* __restrict__ mean, const float* __restrict__ invstd,
+                                                            const float* __restrict__ beta, float* __restrict__ dgamma,
+                                                            float* __restrict__ dbeta, T* dx, T* dres, int acc_dx, int acc_dres,
+                                                            int M, int C, int act) {
+  constexpr int cvb = 4, cb = cvb * V, PLS = WIDE / cvb;
+  __shared__ double red[(WIDE / 64) * 2 * cb], sums[2 * cb];
+  const unsigned char* __restrict__ bits = reinterpret_cast<const unsigned char*>(y);
+  const int CV = C / V, cvl = threadIdx.x % cvb, pl = threadIdx.x / cvb, cv = blockIdx.x * cvb + cvl;
+  const bool live = cv < CV;
+  const int c = live ? cv * V : 0;
+  const float mhi = remask_hi<T>(act), yhi = act == S4TF_ACT_RELU6 ? 6.f : __builtin_inff();
+  Pack<T, V> xv[HOLD], dv[HOLD];
+  float grp[2 * V];
+#pragma unroll
+  for (int e = 0; e < 2 * V; ++e) grp[e] = 0.f;
+  // all loads first; dz replaces dy in place (a zeroed element keeps the storage type exactly)
+#pragma unroll
+  for (int u = 0; u < HOLD; ++u) {
+    const int m = pl + u * PLS;
+    if (live && m < M) {
+      xv[u] = ldp<T, V>(x + (long long)m * C + c);
+      dv[u] = ldp<T, V>(dy + (long long)m * C + c);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < HOLD; ++u) {
+    const int m = pl + u * PLS;
+    if (!live || m >= M) continue;
+    Pack<T, V> yv;
+    unsigned bv = 0;
+    if (MODE == MASK_BITS) bv = bits[(long long)m * CV + cv];
+    else if (MODE == MASK_Y && act != S4TF_ACT_NONE) yv = ldp<T, V>(y + (long long)m * C + c);
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      const float is = invstd[c + e], xc = xv[u].get(e) - mean[c + e];
+      const float z = MODE == MASK_Z ? fmaf(xc, gamma[c + e] * is, beta[c + e]) : 0.f;
+      const float dz = bn_dz<T, V, MODE>(dv[u], yv, bv, z, e, act, mhi, yhi);
+      grp[e] += dz;
+      grp[V + e] += dz * (xc * is);
+      dv[u].set(e, dz);
+    }
+  }
+  wide_sums<V>(grp, cvb, cvl, red, sums);
+  const int c0 = blockIdx.x * cb;
+  if ((int)threadIdx.x < cb && c0 + (int)threadIdx.x < C) {
+    dbeta[c0 + threadIdx.x] = (float)sums[threadIdx.x];
+    dgamma[c0 + threadIdx.x] = (float)sums[cb + threadIdx.x];
+  }
+  if (!live) return;
+  VjpCoef<T, V> k;
+  k.init(mean, invstd, gamma, beta, sums, cb, cvl, c, 1.0f / (float)M, false);
+#pragma unroll
+  for (int u = 0; u < HOLD; ++u) {
+    const int m = pl + u * PLS;
+    if (m >= M) continue;
+    Pack<T, V> ov, av;
+    if (dres && acc_dres) ov = ldp<T, V>(dres + (long long)m * C + c);
+    if (acc_dx) av = ldp<T, V>(dx + (long long)m * C + c);
+    float o[V], r[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      const float dz = dv[u].get(e);
+      o[e] = fmaf(k.gs[e], dz, -fmaf(xv[u].get(e) - k.mu[e], k.a2[e], k.a0[e]));
+      if (acc_dx) o[e] += av.get(e);
+      r[e] = (dres && acc_dres) ? ov.get(e) + dz : dz;
+    }
+    stp<T, V>(dx + (long long)m * C + c, pack_of<T, V>(o));
+    if (dres) stp<T, V>(dres + (long long)m * C + c, pack_of<T, V>(r));
+  }
+}
+
+// The same for a forward pass that has to take its own statistics: x is read once.  Deviations are from the channel's
+// first value, as in bn_stats_kernel.
+template <typename T, int V>
+__global__ __launch_bounds__(WIDE) void bn_fwd_whole_kernel(const T* __restrict__ x, const T* __restrict__ res,
+                                                            const float* __restrict__ gamma, const float* __restrict__ beta,
+                                                            T* __restrict__ y, float* __restrict__ mean, float* __restrict__ invstd,
+                                                            unsigned char* __restrict__ bits, int M, int C, int act, float eps) {
+  constexpr int cvb = 4, cb = cvb * V, PLS = WIDE / cvb;
+  __shared__ double red[(WIDE / 64) * 2 * cb], sums[2 * cb];
+  __shared__ float mul[cb], isl[cb];
+  const int CV = C / V, cvl = threadIdx.x % cvb, pl = threadIdx.x / cvb, cv = blockIdx.x * cvb + cvl;
+  const bool live = cv < CV;
+  const int c = live ? cv * V : 0;
+  Pack<T, V> xv[HOLD];
+  const Pack<T, V> pv = ldp<T, V>(x + c);
+  float grp[2 * V];
+#pragma unroll
+  for (int e = 0; e < 2 * V; ++e) grp[e] = 0.f;
+#pragma unroll
+  for (int u = 0; u < HOLD; ++u) {
+    const int m = pl + u * PLS;
+    if (live && m < M) xv[u] = ldp<T, V>(x + (long long)m * C + c);
+  }
+#pragma unroll
+  for (int u = 0; u < HOLD; ++u) {
+    if (!live || pl + u * PLS >= M) continue;
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      const float d = xv[u].get(e) - pv.get(e);
+      grp[e] += d;
+      grp[V + e] += d * d;
+    }
+  }
+  wide_sums<V>(grp, cvb, cvl, red, sums);
+  const int c0 = blockIdx.x * cb;
+  if ((int)threadIdx.x < cb && c0 + (int)threadIdx.x < C) {
+    const int k = threadIdx.x;
+    const double ms = sums[k] / (double)M;
+    double var = sums[cb + k] / (double)M - ms * ms;
+    if (var < 0.0) var = 0.0;
+    mul[k] = (float)((double)to_f32<T>(x[c0 + k]) + ms);
+    isl[k] = (float)(1.0 / sqrt(var + (double)eps));
+    mean[c0 + k] = mul[k];
+    invstd[c0 + k] = isl[k];
+  }
+  __syncthreads();
+  if (!live) return;
+  const float mhi = remask_hi<T>(act);
+  const float act_lo = act == S4TF_ACT_NONE ? -__builtin_inff() : 0.f;
+  const float act_hi = act == S4TF_ACT_RELU6 ? 6.f : __builtin_inff();
+#pragma unroll
+  for (int u = 0; u < HOLD; ++u) {
+    const int m = pl + u * PLS;
+    if (m >= M) continue;
+    Pack<T, V> rv;
+    if (res) rv = ldp<T, V>(res + (long long)m * C + c);
+    float o[V];
+    unsigned b = 0;
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      float z = bn_z(xv[u].get(e), mul[cvl * V + e], gamma[c + e] * isl[cvl * V + e], beta[c + e]);
+      if (res) z += rv.get(e);
+      o[e] = fminf(fmaxf(z, act_lo), act_hi);
+      b |= (z > 0.f && z < mhi) ? (1u << e) : 0u;
+    }
+    stp<T, V>(y + (long long)m * C + c, pack_of<T, V>(o));
+    if (bits) bits[(long long)m * CV + cv] = (unsigned char)b;
+  }
+}
+
 }  // namespace
 
 // Bytes of the activation bits of an (M, C) tensor: one byte per channel vector and pixel.  The reduction and
@@ -579,6 +1054,32 @@ size_t bn_workspace(size_t M, int C) {
     }                                                                                                           \
   } while (0)
 
+// KERNEL<T, V> with WIDE threads (vectorised channel counts only); WIDE_LAUNCH_MODE: KERNEL<T, V, MODE>
+#define WIDE_LAUNCH(KERNEL, grid, ...)                                                                                  \
+  do {                                                                                                                  \
+    if (d.dtype == S4TF_BF16) {                                                                                         \
+      typedef bf16_t T;                                                                                                 \
+      hipLaunchKernelGGL((KERNEL<T, 8>), grid, dim3(WIDE), 0, st, __VA_ARGS__);                                         \
+    } else {                                                                                                            \
+      typedef float T;                                                                                                  \
+      hipLaunchKernelGGL((KERNEL<T, 4>), grid, dim3(WIDE), 0, st, __VA_ARGS__);                                         \
+    }                                                                                                                   \
+  } while (0)
+#define WIDE_LAUNCH_MODE(KERNEL, mode, grid, ...)                                                                       \
+  do {                                                                                                                  \
+    if (d.dtype == S4TF_BF16) {                                                                                         \
+      typedef bf16_t T;                                                                                                 \
+      if (mode == MASK_BITS) hipLaunchKernelGGL((KERNEL<T, 8, MASK_BITS>), grid, dim3(WIDE), 0, st, __VA_ARGS__);       \
+      else if (mode == MASK_Z) hipLaunchKernelGGL((KERNEL<T, 8, MASK_Z>), grid, dim3(WIDE), 0, st, __VA_ARGS__);        \
+      else hipLaunchKernelGGL((KERNEL<T, 8, MASK_Y>), grid, dim3(WIDE), 0, st, __VA_ARGS__);                            \
+    } else {                                                                                                            \
+      typedef float T;                                                                                                  \
+      if (mode == MASK_BITS) hipLaunchKernelGGL((KERNEL<T, 4, MASK_BITS>), grid, dim3(WIDE), 0, st, __VA_ARGS__);       \
+      else if (mode == MASK_Z) hipLaunchKernelGGL((KERNEL<T, 4, MASK_Z>), grid, dim3(WIDE), 0, st, __VA_ARGS__);        \
+      else hipLaunchKernelGGL((KERNEL<T, 4, MASK_Y>), grid, dim3(WIDE), 0, st, __VA_ARGS__);                            \
+    }                                                                                                                   \
+  } while (0)
+
 int bn_fwd(const s4tf_bn_desc& d, const void* x, const void* res, const float* gamma, const float* beta,
            void* y, float* mean, float* invstd, void* ws, hipStream_t st, const float* stats_part, int stats_rows,
            unsigned char* maskbits) {
@@ -588,6 +1089,23 @@ int bn_fwd(const s4tf_bn_desc& d, const void* x, const void* res, const float* g
   const Plan pa = make_plan((size_t)M, C, d.dtype, 2048, UNROLL);
   float* part = static_cast<float*>(ws);
   int rc;
+  const bool vec = C % (d.dtype == S4TF_BF16 ? 8 : 4) == 0;
+  if (stats_part && stats_rows > 0 && vec) {
+    const int runs = (int)((M + stats_rows - 1) / stats_rows);
+    const Plan pw = make_wide_plan((size_t)M, C, d.dtype, 256);
+    if ((size_t)runs * pw.cvb * pw.V * 2 * sizeof(float) <= MERGE_TABLE_BYTES) {
+      ProfScope ps(PC_BN_APPLY, st);
+      WIDE_LAUNCH(bn_apply_runs_kernel, dim3(pw.cblocks, pw.chunks), (const T*)x, (const T*)res, gamma, beta, stats_part, runs,
+                  stats_rows, d.eps, mean, invstd, (T*)y, maskbits, M, C, pw.cvb, pw.per, d.act);
+      return launch_status("bn_apply_runs");
+    }
+  }
+  if (!(stats_part && stats_rows > 0) && vec && (size_t)M <= HOLD_PIXELS) {
+    ProfScope ps(PC_BN_APPLY, st);
+    WIDE_LAUNCH(bn_fwd_whole_kernel, dim3((C / pa.V + 3) / 4), (const T*)x, (const T*)res, gamma, beta, (T*)y, mean, invstd, maskbits,
+                (int)M, C, d.act, d.eps);
+    return launch_status("bn_fwd_whole");
+  }
   if (stats_part && stats_rows > 0) {
     ProfScope ps(PC_BN_STATS, st);
     const int runs = (int)((M + stats_rows - 1) / stats_rows);
@@ -713,6 +1231,30 @@ int bn_vjp(const s4tf_bn_desc& d, const void* x, const void* y, const float* gam
   const Plan pa = make_plan((size_t)M, C, d.dtype, 2048, UNROLL);
   double* part = static_cast<double*>(ws);
   int rc;
+  if (C % pr.V == 0 && pr.V > 1) {
+    const int mode = maskbits ? MASK_BITS : beta ? MASK_Z : MASK_Y;
+    if ((size_t)M <= HOLD_PIXELS) {
+      ProfScope ps(PC_BN_VJP_APPLY, st);
+      WIDE_LAUNCH_MODE(bn_vjp_whole_kernel, mode, dim3((C / pr.V + 3) / 4), (const T*)x, (const T*)y, (const T*)dy, gamma, mean, invstd,
+                       beta, dgamma, dbeta, (T*)dx, (T*)dres, d.accumulate_dx, d.accumulate_dres, (int)M, C, d.act);
+      return launch_status("bn_vjp_whole");
+    }
+    const Plan pw = make_wide_plan((size_t)M, C, d.dtype, 256);
+    if ((size_t)M * C * dtype_size(d.dtype) <= merge_vjp_tensor_bytes(d.dtype) &&
+        (size_t)pw.chunks * pw.cvb * pw.V * 2 * sizeof(double) <= MERGE_VJP_TABLE_BYTES) {
+      {
+        ProfScope ps(PC_BN_VJP_REDUCE, st);
+        WIDE_LAUNCH_MODE(bn_vjp_reduce_wide_kernel, mode, dim3(pw.cblocks, pw.chunks), (const T*)x, (const T*)y, (const T*)dy, mean,
+                         invstd, gamma, beta, part, M, C, pw.cvb, pw.per, d.act);
+        if ((rc = launch_status("bn_vjp_reduce_wide")) != S4TF_OK) return rc;
+      }
+      ProfScope ps(PC_BN_VJP_APPLY, st);
+      WIDE_LAUNCH_MODE(bn_vjp_apply_wide_kernel, mode, dim3(pw.cblocks, pw.chunks), (const T*)x, (const T*)y, (const T*)dy, gamma, mean,
+                       invstd, beta, part, pw.chunks, dgamma, dbeta, (T*)dx, (T*)dres, d.accumulate_dx, d.accumulate_dres, M, C, pw.cvb,
+                       pw.per, d.act);
+      return launch_status("bn_vjp_apply_wide");
+    }
+  }
   {
     ProfScope ps(PC_BN_VJP_REDUCE, st);
     if (maskbits)

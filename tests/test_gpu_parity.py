@@ -372,6 +372,16 @@ def test_bn_seeded_random_shapes(case, bf16):
 
 
 @pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
+@pytest.mark.parametrize("act,use_res", [("relu", False), ("relu", True), ("none", False)])
+@pytest.mark.parametrize("shape", [
+    (2, 16, 16, 24), (1, 27, 19, 24),    # 512 and 513 pixels: one launch, and the kernels in pieces; channel blocks with a tail
+    (1, 512, 1, 8), (1, 1, 514, 40), (2, 16, 16, 1032),
+    (5, 40, 41, 16), (2, 50, 41, 72), (3, 33, 33, 264)], ids=lambda s: "x".join(map(str, s)))
+def test_bn_small_layers(shape, act, use_res, bf16):
+    test_bn_relu_fwd_and_vjp(shape, act, use_res, bf16)
+
+
+@pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
 @pytest.mark.parametrize("act,use_res", [("none", False), ("relu", False), ("relu", True), ("relu6", True)])
 @pytest.mark.parametrize("shape", BN_SHAPES, ids=lambda s: "x".join(map(str, s)))
 def test_bn_relu_fwd_and_vjp(shape, act, use_res, bf16):
