@@ -141,16 +141,17 @@ int conv_fwd_impl(const s4tf_conv_desc& d, const void* x, const void* w, const f
 // dz: cotangent after the activation pullback
 // The pullback's two halves are independent given dz: the input cotangent, and the parameter gradients.
 int conv_dgrad_impl(const s4tf_conv_desc& d, const void* w, const void* dz, void* dx, hipStream_t st,
-                    const void* acc_src, const unsigned char* acc_bits) {
+                    const void* acc_src, const unsigned char* acc_bits, const void* mask, int mask_act) {
   ConvGeom g = conv_geom(d);
-  if (d.groups == 1) return igemm_dgrad(g, d.dtype, dz, w, dx, d.accumulate_dx, st, acc_src, acc_bits);
+  if (d.groups == 1) return igemm_dgrad(g, d.dtype, dz, w, dx, d.accumulate_dx, st, acc_src, acc_bits, mask, mask_act);
+  if (mask) return fail(S4TF_ERR_UNSUPPORTED, "depthwise dgrad cannot apply an activation's pullback");
   return dwconv_dgrad(g, d.dtype, dz, w, dx, d.accumulate_dx, st);
 }
 int conv_param_grads_impl(const s4tf_conv_desc& d, const void* x, const void* dz, float* dw, float* dbias,
                           void* wg_ws, size_t wg_bytes, hipStream_t st) {
   ConvGeom g = conv_geom(d);
+  if (d.groups == 1) return igemm_wgrad(g, d.dtype, x, dz, dw, wg_ws, wg_bytes, st, dbias);
   if (dbias) CHECK(colsum(d.dtype, dz, (size_t)g.N * g.P * g.Q, g.K, dbias, st, wg_ws, wg_bytes));
-  if (d.groups == 1) return igemm_wgrad(g, d.dtype, x, dz, dw, wg_ws, wg_bytes, st);
   return dwconv_wgrad(g, d.dtype, x, dz, dw, wg_ws, st);
 }
 static int conv_vjp_impl(const s4tf_conv_desc& d, const void* x, const void* w, const void* dz, void* dx, float* dw,

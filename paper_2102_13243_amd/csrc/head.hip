@@ -105,7 +105,7 @@ __global__ __launch_bounds__(256) void head_sample_kernel(const T* __restrict__ 
                                                           const float* __restrict__ b, const int32_t* __restrict__ labels,
                                                           float* __restrict__ pbar, float* __restrict__ z, float* __restrict__ dz,
                                                           float* __restrict__ rowloss, T* dx, int N, int HW, int C, int K,
-                                                          int accumulate) {
+                                                          int accumulate, int mask_act) {
   __shared__ float Wl[SMALL_W], part[SMALL_C > 256 * V ? SMALL_C : 256 * V], dzl[SMALL_K], red[256], sh[4];
   const int n = blockIdx.x, t = threadIdx.x;
   for (int i = t; i < C * K; i += 256) Wl[i] = W[i];
@@ -156,6 +156,7 @@ __global__ __launch_bounds__(256) void head_sample_kernel(const T* __restrict__ 
     float d = 0.f;
     for (int l = 0; l < K; ++l) d = fmaf(dzl[l], Wl[c * K + l], d);
     part[c] = d / hw;
+    if (mask_act) part[c] *= act_mask(to_f32<T>(x[(long long)n * C + c]), mask_act);  // HW is 1, see head_can_mask
   }
   __syncthreads();
   T* out = dx + (long long)n * HW * C;
@@ -416,8 +417,9 @@ Layout layout(const s4tf_head_desc& d) {
 
 size_t head_workspace(const s4tf_head_desc& d) { return layout(d).total; }
 
+bool head_can_mask(const s4tf_head_desc& d) { return small_head(d) && d.h * d.w == 1 && !d.accumulate_dx; }
 int head_value(const s4tf_head_desc& d, const void* x, const float* W, const float* b, const int32_t* labels, void* dx,
-               float* logits_out, void* ws, hipStream_t st) {
+               float* logits_out, void* ws, hipStream_t st, int mask_act) {
   const Layout l = layout(d);
   char* base = static_cast<char*>(ws);
   float* pbar = reinterpret_cast<float*>(base + l.pbar);
@@ -431,7 +433,7 @@ int head_value(const s4tf_head_desc& d, const void* x, const float* W, const flo
   if (small_head(d)) {
     ProfScope ps(PC_HEAD, st);
     HEAD_LAUNCH(head_sample_kernel, dim3(d.n), (const T*)x, W, b, labels, pbar, logits, dz, rowloss, (T*)dx, d.n, HW, d.c, d.classes,
-                d.accumulate_dx);
+                d.accumulate_dx, mask_act);
     return launch_status("head_sample");
   }
   // channel vectors per workgroup of the pooling kernels: 64, and narrower where that leaves the chip empty
@@ -461,7 +463,7 @@ int head_value(const s4tf_head_desc& d, const void* x, const float* W, const flo
   if (!dx) return S4TF_OK;
   ProfScope ps(PC_HEAD, st);  // dpbar[n][c] = sum_j dz[n][j] W[c][j]
   if (waves) {
-    if ((rc = wave_gemm_dgrad(g, dz, W, part, 0, st)) != S4TF_OK) return rc;
+    if ((rc = wave_gemm_dgrad(g, dz, W, part, 0, nullptr, S4TF_ACT_NONE, st)) != S4TF_OK) return rc;
   } else {
     hipLaunchKernelGGL(skinny_gemm_kernel<true>, sb.grid, dim3(256), 0, st, dz, W, part, d.n, d.c, d.classes, sb.kper);
     if ((rc = launch_status("head dpbar")) != S4TF_OK) return rc;

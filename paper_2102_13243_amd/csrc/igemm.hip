@@ -889,6 +889,9 @@ int igemm_fwd(const ConvGeom& g, int dtype, const void* x, const void* w, const 
   const bool with_stats = stats_part && stats_rows && !bias && act == S4TF_ACT_NONE;
   if (patchconv_fwd_ok(g, dtype) && aligned16(x) && aligned16(w) && aligned16(y))  // few channels, 3x3: out of an LDS patch
     return patchconv_fwd(g, x, w, bias, act, y, with_stats ? stats_part : nullptr, with_stats ? stats_rows : nullptr, st);
+  if (small_conv_ok(PASS_FWD, g, dtype))
+    return small_conv_fwd(g, static_cast<const float*>(x), static_cast<const float*>(w), bias, act, static_cast<float*>(y),
+                          with_stats ? stats_part : nullptr, with_stats ? stats_rows : nullptr, st);
   if (wave_gemm_ok(PASS_FWD, g, dtype) && aligned16(x) && aligned16(w) && aligned16(y))
     return wave_gemm_fwd(g, static_cast<const float*>(x), static_cast<const float*>(w), bias, act, static_cast<float*>(y),
                       with_stats ? stats_part : nullptr, with_stats ? stats_rows : nullptr, st);
@@ -917,9 +920,15 @@ bool igemm_dgrad_can_add_other(const ConvGeom& g, int dtype) {
   return dtype == S4TF_BF16 && g.stride == 1 && g.C % 8 == 0 && igemm_dma_geom_ok(PASS_DGRAD, g);
 }
 
+// Can igemm_dgrad multiply its result by an activation's derivative?  For 16-byte aligned operands.
+bool igemm_dgrad_can_mask(const ConvGeom& g, int dtype) {
+  return small_conv_ok(PASS_DGRAD, g, dtype) || (!patchconv_dgrad_ok(g, dtype) && wave_gemm_ok(PASS_DGRAD, g, dtype));
+}
+
 int igemm_dgrad(const ConvGeom& g, int dtype, const void* dy, const void* w, void* dx, int accumulate,
-                hipStream_t st, const void* acc_src, const unsigned char* acc_bits) {
+                hipStream_t st, const void* acc_src, const unsigned char* acc_bits, const void* mask, int mask_act) {
   Args a = {};
+  if (mask && !igemm_dgrad_can_mask(g, dtype)) return fail(S4TF_ERR_UNSUPPORTED, "dgrad: this shape cannot apply an activation's pullback");
   a.g = g; a.a = dy; a.b = w; a.out = dx; a.accumulate = accumulate;
   if (acc_src) {
     if (!igemm_dgrad_adds_other(g, dtype, dy, w, dx, acc_src))
@@ -970,15 +979,20 @@ int igemm_dgrad(const ConvGeom& g, int dtype, const void* dy, const void* w, voi
     fill_tiles(a, 128, 128, Cfg<bf16_t>::BK);
     return launch<bf16_t, PASS_DGRAD>(a, 1, st);
   }
+  if (small_conv_ok(PASS_DGRAD, g, dtype))
+    return small_conv_dgrad(g, static_cast<const float*>(dy), static_cast<const float*>(w), static_cast<float*>(dx), accumulate,
+                            static_cast<const float*>(mask), mask_act, st);
   if (patchconv_dgrad_ok(g, dtype) && aligned16(dy) && aligned16(w) && aligned16(dx))
     return patchconv_dgrad(g, dy, w, dx, accumulate, st);
   if (wave_gemm_ok(PASS_DGRAD, g, dtype) && aligned16(dy) && aligned16(w) && aligned16(dx))
-    return wave_gemm_dgrad(g, static_cast<const float*>(dy), static_cast<const float*>(w), static_cast<float*>(dx), accumulate, st);
+    return wave_gemm_dgrad(g, static_cast<const float*>(dy), static_cast<const float*>(w), static_cast<float*>(dx), accumulate,
+                           static_cast<const float*>(mask), mask_act, st);
   fill_tiles_f32(a, false);
   return launch<float, PASS_DGRAD>(a, 1, st);
 }
 
 size_t igemm_wgrad_workspace(const ConvGeom& g, int dtype) {
+  if (small_conv_ok(PASS_WGRAD, g, dtype)) return small_wgrad_workspace(g);
   int splits, per;
   if (wave_gemm_ok(PASS_WGRAD, g, dtype)) splits = wave_gemm_wgrad_splits(g);
   else wgrad_split(g, dtype, splits, per);
@@ -987,7 +1001,12 @@ size_t igemm_wgrad_workspace(const ConvGeom& g, int dtype) {
 }
 
 int igemm_wgrad(const ConvGeom& g, int dtype, const void* x, const void* dy, float* dw, void* ws,
-                size_t ws_bytes, hipStream_t st) {
+                size_t ws_bytes, hipStream_t st, float* db) {
+  if (small_conv_ok(PASS_WGRAD, g, dtype)) {
+    const size_t need = small_wgrad_workspace(g);
+    if (ws_bytes < need) return fail(S4TF_ERR_WORKSPACE, "wgrad needs %zu workspace bytes, got %zu", need, ws_bytes);
+    return small_wgrad(g, static_cast<const float*>(x), static_cast<const float*>(dy), dw, db, ws, st);
+  }
   Args a = {};
   a.g = g; a.a = x; a.b = dy;
   a.Mg = g.R * g.S * g.C; a.Ng = g.K; a.Kg = g.N * g.P * g.Q;
@@ -998,12 +1017,17 @@ int igemm_wgrad(const ConvGeom& g, int dtype, const void* x, const void* dy, flo
   if (waves) splits = wave_gemm_wgrad_splits(g);
   else wgrad_split(g, dtype, splits, per);
   const long long n = (long long)a.Mg * a.Ng;
+  const bool with_bias = waves && wave_gemm_bias_ok(g);
+  if (db && !with_bias) {  // its partial sums lie where the filter gradient's will
+    const int rc = colsum(dtype, dy, (size_t)a.Kg, a.Ng, db, st, ws, ws_bytes);
+    if (rc != S4TF_OK) return rc;
+  }
   if (splits > 1 && ws_bytes < (size_t)splits * n * sizeof(float))
     return fail(S4TF_ERR_WORKSPACE, "wgrad needs %zu workspace bytes, got %zu", (size_t)splits * n * sizeof(float), ws_bytes);
   int rc;
   if (waves) {
     ProfScope ps(PC_CONV_WGRAD, st);
-    rc = wave_gemm_wgrad(g, static_cast<const float*>(x), static_cast<const float*>(dy), splits > 1 ? static_cast<float*>(ws) : dw, st);
+    rc = wave_gemm_wgrad(g, static_cast<const float*>(x), static_cast<const float*>(dy), splits > 1 ? static_cast<float*>(ws) : dw, with_bias ? db : nullptr, st);
   } else {
     if (dtype == S4TF_BF16) fill_tiles(a, 128, 128, Cfg<bf16_t>::BK);
     else fill_tiles_f32(a, true);

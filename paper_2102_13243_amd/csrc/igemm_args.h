@@ -88,8 +88,19 @@ int igemm_dma_launch(int pass, Args& a, int splits, hipStream_t st);
 bool wave_gemm_ok(int pass, const ConvGeom& g, int dtype);
 int wave_gemm_fwd(const ConvGeom& g, const float* x, const float* w, const float* bias, int act, float* y, float* stats,
                   int* stats_rows, hipStream_t st);
-int wave_gemm_dgrad(const ConvGeom& g, const float* dy, const float* w, float* dx, int accumulate, hipStream_t st);
+int wave_gemm_dgrad(const ConvGeom& g, const float* dy, const float* w, float* dx, int accumulate, const float* mask, int mask_act,
+                    hipStream_t st);
 int wave_gemm_wgrad_splits(const ConvGeom& g);
-int wave_gemm_wgrad(const ConvGeom& g, const float* x, const float* dy, float* out, hipStream_t st);
+bool wave_gemm_bias_ok(const ConvGeom& g);
+int wave_gemm_wgrad(const ConvGeom& g, const float* x, const float* dy, float* out, float* db, hipStream_t st);
+
+// fp32, few channels (smallconv.hip)
+bool small_conv_ok(int pass, const ConvGeom& g, int dtype);
+int small_conv_fwd(const ConvGeom& g, const float* x, const float* w, const float* bias, int act, float* y, float* stats,
+                   int* stats_rows, hipStream_t st);
+int small_conv_dgrad(const ConvGeom& g, const float* dy, const float* w, float* dx, int accumulate, const float* mask, int mask_act,
+                     hipStream_t st);
+size_t small_wgrad_workspace(const ConvGeom& g);
+int small_wgrad(const ConvGeom& g, const float* x, const float* dy, float* dw, float* db, void* ws, hipStream_t st);
 
 }  // namespace s4tf

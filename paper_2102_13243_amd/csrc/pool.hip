@@ -31,7 +31,8 @@ __global__ void avgpool2_fwd_kernel(const T* __restrict__ x, T* __restrict__ y, 
   }
 }
 template <typename T>
-__global__ void avgpool2_vjp_kernel(const T* __restrict__ dy, T* __restrict__ dx, int N, int H, int W, int C, int accumulate) {
+__global__ void avgpool2_vjp_kernel(const T* __restrict__ dy, const T* __restrict__ x, T* __restrict__ dx, int N, int H, int W, int C,
+                                    int accumulate, int mask_act) {
   const int P = H / 2, Q = W / 2;
   const long long total = (long long)N * H * W * C;
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (long long)gridDim.x * blockDim.x) {
@@ -44,6 +45,7 @@ __global__ void avgpool2_vjp_kernel(const T* __restrict__ dy, T* __restrict__ dx
     float v = 0.f;
     if (p < P && q < Q) v = to_f32<T>(dy[(((long long)n * P + p) * Q + q) * C + c]) * 0.25f;
     if (accumulate) v += to_f32<T>(dx[i]);
+    if (mask_act) v *= act_mask(to_f32<T>(x[i]), mask_act);
     dx[i] = from_f32<T>(v);
   }
 }
@@ -641,7 +643,7 @@ int pool_fwd(const s4tf_pool_desc& d, const void* x, void* y, hipStream_t st, un
   return launch_status("pool_fwd");
 }
 
-int pool_vjp(const s4tf_pool_desc& d, const void* x, const void* dy, void* dx, hipStream_t st, const unsigned char* idx) {
+int pool_vjp(const s4tf_pool_desc& d, const void* x, const void* dy, void* dx, hipStream_t st, const unsigned char* idx, int mask_act) {
   ProfScope ps(PC_POOL, st);
   if (idx && pool_saves_positions(d) && aligned16(x) && aligned16(dy) && aligned16(dx)) {  // the forward pass's own conditions
     const long long cells = (long long)d.n * ((d.h + 1) / 2) * ((d.w + 1) / 2);
@@ -665,12 +667,12 @@ int pool_vjp(const s4tf_pool_desc& d, const void* x, const void* dy, void* dx, h
   }
   if (d.dtype == S4TF_BF16) {
     typedef bf16_t T;
-    if (avg) hipLaunchKernelGGL(avgpool2_vjp_kernel<T>, grid, block, 0, st, (const T*)dy, (T*)dx, d.n, d.h, d.w, d.c, d.accumulate_dx);
+    if (avg) hipLaunchKernelGGL(avgpool2_vjp_kernel<T>, grid, block, 0, st, (const T*)dy, (const T*)x, (T*)dx, d.n, d.h, d.w, d.c, d.accumulate_dx, mask_act);
     else if (vec) hipLaunchKernelGGL((maxpool3s2_vjp_kernel<T, 8>), vgrid, block, 0, st, (const T*)x, (const T*)dy, (T*)dx, d.n, d.h, d.w, d.c, d.accumulate_dx);
     else hipLaunchKernelGGL((maxpool3s2_vjp_kernel<T, 1>), grid, block, 0, st, (const T*)x, (const T*)dy, (T*)dx, d.n, d.h, d.w, d.c, d.accumulate_dx);
   } else {
     typedef float T;
-    if (avg) hipLaunchKernelGGL(avgpool2_vjp_kernel<T>, grid, block, 0, st, (const T*)dy, (T*)dx, d.n, d.h, d.w, d.c, d.accumulate_dx);
+    if (avg) hipLaunchKernelGGL(avgpool2_vjp_kernel<T>, grid, block, 0, st, (const T*)dy, (const T*)x, (T*)dx, d.n, d.h, d.w, d.c, d.accumulate_dx, mask_act);
     else if (vec) hipLaunchKernelGGL((maxpool3s2_vjp_kernel<T, 4>), vgrid, block, 0, st, (const T*)x, (const T*)dy, (T*)dx, d.n, d.h, d.w, d.c, d.accumulate_dx);
     else hipLaunchKernelGGL((maxpool3s2_vjp_kernel<T, 1>), grid, block, 0, st, (const T*)x, (const T*)dy, (T*)dx, d.n, d.h, d.w, d.c, d.accumulate_dx);
   }

@@ -101,14 +101,18 @@ int patchconv_dgrad(const ConvGeom& g, const void* dy, const void* w, void* dx, 
 // acc_src (optional; only where igemm_dgrad_adds_other says so): the result is dgrad + acc_src instead of
 // dgrad (+ old dx); acc_bits (optional): activation bits as bn_fwd leaves them, one per element of acc_src,
 // elements whose bit is clear add nothing.
+// mask (optional; only where igemm_dgrad_can_mask says so): the layer's input; the result (with what it is added to) is
+// multiplied by the derivative of mask_act there, the pullback of the activation that made the input.
 int igemm_dgrad(const ConvGeom& g, int dtype, const void* dy, const void* w, void* dx, int accumulate,
-                hipStream_t st, const void* acc_src = nullptr, const unsigned char* acc_bits = nullptr);
+                hipStream_t st, const void* acc_src = nullptr, const unsigned char* acc_bits = nullptr, const void* mask = nullptr,
+                int mask_act = S4TF_ACT_NONE);
+bool igemm_dgrad_can_mask(const ConvGeom& g, int dtype);
 bool igemm_dgrad_adds_other(const ConvGeom& g, int dtype, const void* dy, const void* w, const void* dx,
                             const void* acc_src);
 bool igemm_dgrad_can_add_other(const ConvGeom& g, int dtype);  // the same question for 16-byte aligned operands
 size_t igemm_wgrad_workspace(const ConvGeom& g, int dtype);
 int igemm_wgrad(const ConvGeom& g, int dtype, const void* x, const void* dy, float* dw, void* ws,
-                size_t ws_bytes, hipStream_t st);
+                size_t ws_bytes, hipStream_t st, float* db = nullptr);  // db: also the column sums of dy, the bias gradient
 
 // depthwise (groups == C == K)
 int dwconv_fwd(const ConvGeom& g, int dtype, const void* x, const void* w, const float* bias, int act,
@@ -169,13 +173,17 @@ int bn_vjp(const s4tf_bn_desc& d, const void* x, const void* y, const float* gam
 // output element, written by pool_fwd, the window position of the maximum; pool_vjp given it does not read x
 bool pool_saves_positions(const s4tf_pool_desc& d);
 int pool_fwd(const s4tf_pool_desc& d, const void* x, void* y, hipStream_t st, unsigned char* idx = nullptr);
-int pool_vjp(const s4tf_pool_desc& d, const void* x, const void* dy, void* dx, hipStream_t st, const unsigned char* idx = nullptr);
+// mask_act (average pool only): dx is also multiplied by the derivative of the activation that made x
+int pool_vjp(const s4tf_pool_desc& d, const void* x, const void* dy, void* dx, hipStream_t st, const unsigned char* idx = nullptr,
+             int mask_act = S4TF_ACT_NONE);
 
 // head.  head_value: logits, cotangents of the logits (kept in ws) and dx; head_params: loss, dW and db from what it left in ws
-// (possibly on another stream, ordered behind it); head_fwd_vjp: both.
+// (possibly on another stream, ordered behind it); head_fwd_vjp: both.  mask_act (only where head_can_mask says so): dx is also
+// multiplied by the derivative of the activation that made x.
+bool head_can_mask(const s4tf_head_desc& d);
 size_t head_workspace(const s4tf_head_desc& d);
 int head_value(const s4tf_head_desc& d, const void* x, const float* W, const float* b, const int32_t* labels, void* dx,
-               float* logits, void* ws, hipStream_t st);
+               float* logits, void* ws, hipStream_t st, int mask_act = S4TF_ACT_NONE);
 int head_params(const s4tf_head_desc& d, float* loss, float* dW, float* db, void* ws, hipStream_t st);
 int head_fwd_vjp(const s4tf_head_desc& d, const void* x, const float* W, const float* b, const int32_t* labels, float* loss,
                  void* dx, float* dW, float* db, float* logits, void* ws, hipStream_t st);
@@ -211,7 +219,8 @@ int check_ws(const void* ws, size_t have, size_t want);
 int conv_fwd_impl(const s4tf_conv_desc& d, const void* x, const void* w, const float* bias, void* y, hipStream_t st,
                   float* stats_part = nullptr, int* stats_rows = nullptr);
 int conv_dgrad_impl(const s4tf_conv_desc& d, const void* w, const void* dz, void* dx, hipStream_t st,
-                    const void* acc_src = nullptr, const unsigned char* acc_bits = nullptr);
+                    const void* acc_src = nullptr, const unsigned char* acc_bits = nullptr, const void* mask = nullptr,
+                    int mask_act = S4TF_ACT_NONE);
 int conv_param_grads_impl(const s4tf_conv_desc& d, const void* x, const void* dz, float* dw, float* dbias,
                           void* wg_ws, size_t wg_bytes, hipStream_t st);
 

@@ -79,6 +79,7 @@ struct NetPlan {
   // BatchNorm need not write its residual cotangent dz = act'(y) dy: the convolution's dgrad adds it from dy
   // and the bits in its epilogue (same values, one tensor less written).
   std::vector<int> defer_conv;
+  std::vector<char> masked;  // per convolution: its consumer's pullback multiplies by the activation's derivative
   std::vector<size_t> mask_off;      // per op: activation bits of a BatchNorm with residual and activation (0: none)
   std::vector<size_t> stat_off;      // per op: save_mean/invstd (BN); max pool: the saved window positions (one byte per output)
   // a convolution on the batch itself whose channel count is not a multiple of 8 (bf16) or 4 (fp32) runs
@@ -137,6 +138,7 @@ int plan_net(const s4tf_net_desc* net, NetPlan& pl) {
   pl.stat_off.assign(nops, 0);
   pl.mask_off.assign(nops, 0);
   pl.defer_conv.assign(nops, -1);
+  pl.masked.assign(nops, 0);
   pl.pad_c.assign(nops, 0);
   pl.fold.assign(nops, 0);
   pl.xpad_off.assign(nops, 0);
@@ -167,9 +169,11 @@ int plan_net(const s4tf_net_desc* net, NetPlan& pl) {
         if (op.has_bias) add_param(i, 1, (size_t)op.k);
         // channel count of the batch not a multiple of the 16-byte loaders' vector (8 bf16, 4 fp32): padded copies
         const int vecw = net->dtype == S4TF_BF16 ? 8 : 4;
-        // (fp32: only where the convolution is big enough to repay the two copy launches)
+        // (fp32: only where the convolution is big enough to repay the two copy launches, and too wide for the kernels that
+        // take any channel count, smallconv.hip)
         if (in.root == 0 && op.groups == 1 && in.c % vecw != 0 &&
-            (net->dtype == S4TF_BF16 || (op.k % 4 == 0 && (long long)g.N * g.P * g.Q >= 32768))) {
+            (net->dtype == S4TF_BF16 || (op.k % 4 == 0 && (long long)g.N * g.P * g.Q >= 32768 &&
+                                          !(small_conv_ok(PASS_FWD, g, net->dtype) && small_conv_ok(PASS_WGRAD, g, net->dtype))))) {
           pl.pad_c[i] = (int)align_up((size_t)in.c, vecw);
           g.C = pl.pad_c[i];
           if (net->dtype == S4TF_BF16 && op.stride == 2 && in.c <= 4 && op.r >= 3 && op.s >= 3 && (op.r & 1) && (op.s & 1) &&
@@ -289,6 +293,25 @@ int plan_net(const s4tf_net_desc* net, NetPlan& pl) {
       pl.wpad_off[i] = off; off += align_up(taps * pl.pad_c[i] * op.k * es, 256);
       pl.dwpad_off[i] = off; off += align_up(taps * pl.pad_c[i] * op.k * sizeof(float), 256);
     }
+  // A convolution's activation: where its output has one consumer whose pullback can multiply by the derivative while it
+  // writes that output's cotangent, it does (the pass of its own costs a launch and three passes over the tensor)
+  for (int j = 0; j < nops; ++j) {
+    const s4tf_op& op = net->ops[j];
+    const int i = op.in - 1;
+    if (i < 0 || net->ops[i].kind != S4TF_OP_CONV || net->ops[i].act == S4TF_ACT_NONE || pl.t[op.in].consumers != 1 ||
+        pl.t[op.in].root != op.in)
+      continue;
+    const TensorPlan& in = pl.t[op.in];
+    if (op.kind == S4TF_OP_CONV) {
+      const s4tf_conv_desc d = {in.n, in.h, in.w, in.c, op.k, op.r, op.s, op.stride, op.pad, op.groups, net->dtype, op.act, 0};
+      pl.masked[i] = op.groups == 1 && igemm_dgrad_can_mask(conv_geom(d), net->dtype);
+    } else if (op.kind == S4TF_OP_AVGPOOL2) {
+      pl.masked[i] = 1;
+    } else if (op.kind == S4TF_OP_HEAD) {
+      const s4tf_head_desc d = {in.n, in.h, in.w, in.c, op.k, net->dtype};
+      pl.masked[i] = head_can_mask(d);
+    }
+  }
   double conv_flops = 0.0;  // forward pass
   for (int i = 0; i < nops; ++i)
     if (net->ops[i].kind == S4TF_OP_CONV) {
@@ -497,7 +520,7 @@ int record_schedule(s4tf_net& N) {
     }
     switch (op.kind) {
       case S4TF_OP_CONV: {
-        if (op.act != S4TF_ACT_NONE) emit(K_ACT_VJP, on_side, on_side, i);  // in place: dy is not needed once dz exists
+        if (op.act != S4TF_ACT_NONE && !pl.masked[i]) emit(K_ACT_VJP, on_side, on_side, i);  // in place: dy is not needed once dz exists
         // dz is final.  The input cotangent is computed first; the parameter gradients go to the side
         // stream and start when it is done, so that they run beside the bandwidth-bound BatchNorm pullback
         // of the layer before rather than beside this layer's other matrix kernel (measured: 2 % of the step).
@@ -681,6 +704,8 @@ int run_step(const s4tf_net& N, s4tf_params* params, const s4tf_batch* batch, fl
     return bf16 ? (const void*)(static_cast<bf16_t*>(params->lowp) + pl.poff[2 * op])
                 : (const void*)(params->master + pl.poff[2 * op]);
   };
+  // the activation whose derivative the pullback that writes tensor t's cotangent multiplies by
+  auto masking = [&](int t) -> int { return t > 0 && pl.masked[t - 1] ? net->ops[t - 1].act : (int)S4TF_ACT_NONE; };
   auto conv_desc = [&](int i, int accumulate) {
     const s4tf_op& op = net->ops[i];
     const TensorPlan& in = pl.t[op.in];
@@ -761,8 +786,9 @@ int run_step(const s4tf_net& N, s4tf_params* params, const s4tf_batch* batch, fl
         const TensorPlan& in = pl.t[op.in];
         s4tf_head_desc d = {in.n, in.h, in.w, in.c, op.k, dt};
         void* dx = c.a == 0 ? nullptr : grad_ptr(c.a);
+        const int mask_act = masking(op.in);
         CHECK(head_value(d, act_ptr(op.in), params->master + pl.poff[2 * i], params->master + pl.poff[2 * i + 1], batch->labels, dx,
-                         nullptr, ws + pl.head_off, s));
+                         nullptr, ws + pl.head_off, s, mask_act));
         if (c.b == 1)
           CHECK(head_params(d, batch->loss, params->grad + pl.poff[2 * i], params->grad + pl.poff[2 * i + 1], ws + pl.head_off, s));
         break;
@@ -784,7 +810,8 @@ int run_step(const s4tf_net& N, s4tf_params* params, const s4tf_batch* batch, fl
           CHECK(conv_dgrad_impl(d, conv_w(i), grad_ptr(i + 1), grad_ptr(src), s, grad_ptr(c.b + 1),
                                 reinterpret_cast<const unsigned char*>(ws + pl.mask_off[c.b])));
         else
-          CHECK(conv_dgrad_impl(d, conv_w(i), grad_ptr(i + 1), grad_ptr(src), s));
+          CHECK(conv_dgrad_impl(d, conv_w(i), grad_ptr(i + 1), grad_ptr(src), s, nullptr, nullptr, masking(src) ? act_ptr(src) : nullptr,
+                                masking(src)));
         break;
       }
       case K_PARAM_GRADS: {  // filter (and bias) gradient of convolution i
@@ -831,7 +858,7 @@ int run_step(const s4tf_net& N, s4tf_params* params, const s4tf_batch* batch, fl
         const int src = in.root;
         s4tf_pool_desc d = {in.n, in.h, in.w, in.c, op.kind == S4TF_OP_AVGPOOL2 ? S4TF_POOL_AVG2 : S4TF_POOL_MAX3S2, dt, c.a};
         const unsigned char* pos = pool_saves_positions(d) ? reinterpret_cast<const unsigned char*>(ws + pl.stat_off[i]) : nullptr;
-        CHECK(pool_vjp(d, act_ptr(src), grad_ptr(i + 1), grad_ptr(src), s, pos));
+        CHECK(pool_vjp(d, act_ptr(src), grad_ptr(i + 1), grad_ptr(src), s, pos, masking(src)));
         break;
       }
       case K_SGD: {

@@ -38,6 +38,8 @@ struct WaveArgs {
   const float* b;
   float* out;
   const float* bias;  // forward, optional
+  const float* mask;  // dgrad, optional: the layer's input, the result is multiplied by the derivative of the activation that made it
+  float* db;          // wgrad, optional: column sums of b
   float* stats;       // forward, optional: BatchNorm partial sums per run of one workgroup's rows, see igemm_fwd
   int M, N, K;        // K: channels per tap (forward, dgrad), pixels (wgrad)
   int C;              // wgrad: channels of x
@@ -98,6 +100,25 @@ __global__ __launch_bounds__(64 * WM * WK, 2) void wave_gemm_kernel(const WaveAr
   // columns fastest, so that what neighbours share stays in one L2.
   const int tiles = g.tiles_m * g.tiles_n, units = tiles * g.splits, per = (units + NUM_XCD - 1) / NUM_XCD;
   const int u = (int)(blockIdx.x % NUM_XCD) * per + (int)(blockIdx.x / NUM_XCD);
+  if constexpr (PASS == PASS_WGRAD) {
+    if ((int)(blockIdx.x / NUM_XCD) >= per) {  // behind the last tile: workgroups that sum 16 columns of dy each, the bias gradient
+      constexpr int LANES = 4 * WM * WK;
+      double* sh = reinterpret_cast<double*>(smem);
+      const int c = threadIdx.x & 15, l = threadIdx.x >> 4, col = ((int)blockIdx.x - NUM_XCD * per) * 16 + c;
+      double s = 0.0;  // bias cotangents cancel heavily: in double
+      if (col < g.N) {
+#pragma unroll 4
+        for (int px = l; px < g.K; px += LANES) s += (double)g.b[(long long)px * g.N + col];
+      }
+      sh[threadIdx.x] = s;
+      __syncthreads();
+      if (l == 0 && col < g.N) {
+        for (int i = 1; i < LANES; ++i) s += sh[i * 16 + c];
+        g.db[col] = (float)s;
+      }
+      return;
+    }
+  }
   if ((int)(blockIdx.x / NUM_XCD) >= per || u >= units) return;
   const int split = u / tiles, t = u - split * tiles, tm = t / g.tiles_n, tn = t - tm * g.tiles_n;
   const int m0 = tm * BM + wm * FM * 16, n0 = tn * BN;
@@ -376,13 +397,15 @@ __global__ __launch_bounds__(64 * WM * WK, 2) void wave_gemm_kernel(const WaveAr
         const int row = m0 + row_of(i, v);
         if (row >= g.M) continue;
         V* dst = reinterpret_cast<V*>(out + (long long)row * g.N + col);
-        V o, old;
+        V o, old, y;
         if (PASS == PASS_DGRAD && g.accumulate) old = *dst;
+        if (PASS == PASS_DGRAD && g.mask) y = *reinterpret_cast<const V*>(g.mask + (long long)row * g.N + col);
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
           float val = acc[i][j][v];
           if constexpr (PASS == PASS_FWD) val = fminf(fmaxf(val + bias[j], lo), hi);
           if (PASS == PASS_DGRAD && g.accumulate) val += elem<FN>(old, j);
+          if (PASS == PASS_DGRAD && g.mask) val *= act_mask(elem<FN>(y, j), g.act);
           if constexpr (FN == 1) o = val; else o[j] = val;
         }
         *dst = o;
@@ -397,8 +420,10 @@ __global__ __launch_bounds__(64 * WM * WK, 2) void wave_gemm_kernel(const WaveAr
         for (int v = 0; v < 4; ++v) {
           const int row = m0 + row_of(i, v);
           if (row >= g.M) continue;
-          float* dst = out + (long long)row * g.N + col + j;
-          *dst = g.accumulate ? acc[i][j][v] + *dst : acc[i][j][v];
+          const long long at = (long long)row * g.N + col + j;
+          float val = g.accumulate ? acc[i][j][v] + out[at] : acc[i][j][v];
+          if (PASS == PASS_DGRAD && g.mask) val *= act_mask(g.mask[at], g.act);
+          out[at] = val;
         }
     }
   }
@@ -453,8 +478,8 @@ template <int PASS, bool POINT, int FN, int WM, int WK> int launch_wave(WaveArgs
   a.tiles_m = (a.M + WM * FM * 16 - 1) / (WM * FM * 16);
   a.tiles_n = (a.N + FN * 16 - 1) / (FN * 16);
   a.splits = splits;
-  const int units = a.tiles_m * a.tiles_n * splits;
-  hipLaunchKernelGGL((wave_gemm_kernel<PASS, POINT, FN, WM, WK, stages_of(PASS)>), dim3(NUM_XCD * ((units + NUM_XCD - 1) / NUM_XCD)),
+  const int units = a.tiles_m * a.tiles_n * splits, bias = PASS == PASS_WGRAD && a.db ? (a.N + 15) / 16 : 0;
+  hipLaunchKernelGGL((wave_gemm_kernel<PASS, POINT, FN, WM, WK, stages_of(PASS)>), dim3(NUM_XCD * ((units + NUM_XCD - 1) / NUM_XCD) + bias),
                      dim3(64 * WM * WK), 0, st, a);
   return launch_status("wave_gemm");
 }
@@ -516,9 +541,11 @@ int wave_gemm_fwd(const ConvGeom& g, const float* x, const float* w, const float
   return launch_wave<PASS_FWD>(p, is_point(g), a, st);
 }
 
-int wave_gemm_dgrad(const ConvGeom& g, const float* dy, const float* w, float* dx, int accumulate, hipStream_t st) {
+// mask (optional): the layer's own input; dx is then multiplied by act'(mask), the pullback of the activation that made it
+int wave_gemm_dgrad(const ConvGeom& g, const float* dy, const float* w, float* dx, int accumulate, const float* mask, int mask_act,
+                    hipStream_t st) {
   WaveArgs a = {};
-  a.a = dy; a.b = w; a.out = dx; a.accumulate = accumulate;
+  a.a = dy; a.b = w; a.out = dx; a.accumulate = accumulate; a.mask = mask; a.act = mask_act;
   a.M = g.N * g.H * g.W; a.N = g.C; a.K = a.C = g.K;
   a.H = g.P; a.W = g.Q; a.S = g.S; a.stride = g.stride; a.pad = g.pad; a.P = g.H; a.Q = g.W; a.taps = g.R * g.S;
   a.a_bytes = 4u * (unsigned)(g.N * g.P * g.Q * g.K);
@@ -526,12 +553,15 @@ int wave_gemm_dgrad(const ConvGeom& g, const float* dy, const float* w, float* d
   return launch_wave<PASS_DGRAD>(plan_of(PASS_DGRAD, g), is_point(g), a, st);
 }
 
+// Up to 4096 pixels a workgroup's walk down 16 columns is shorter than the tiles beside it (dense layers at batch 128: the
+// separate column sum took 8 us, this nothing that shows); longer ones need the two-stage sum.
+bool wave_gemm_bias_ok(const ConvGeom& g) { return (long long)g.N * g.P * g.Q < 4096; }
 int wave_gemm_wgrad_splits(const ConvGeom& g) { return plan_of(PASS_WGRAD, g).splits; }
 
-// `out`: wave_gemm_wgrad_splits(g) slabs of (R, S, C, K)
-int wave_gemm_wgrad(const ConvGeom& g, const float* x, const float* dy, float* out, hipStream_t st) {
+// `out`: wave_gemm_wgrad_splits(g) slabs of (R, S, C, K); db (optional, see wave_gemm_bias_ok): the bias gradient
+int wave_gemm_wgrad(const ConvGeom& g, const float* x, const float* dy, float* out, float* db, hipStream_t st) {
   WaveArgs a = {};
-  a.a = x; a.b = dy; a.out = out;
+  a.a = x; a.b = dy; a.out = out; a.db = db;
   a.M = g.R * g.S * g.C; a.N = g.K; a.K = g.N * g.P * g.Q; a.C = g.C;
   a.H = g.H; a.W = g.W; a.S = g.S; a.stride = g.stride; a.pad = g.pad; a.P = g.P; a.Q = g.Q; a.taps = g.R * g.S;
   a.a_bytes = 4u * (unsigned)(g.N * g.H * g.W * g.C);

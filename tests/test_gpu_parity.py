@@ -192,6 +192,20 @@ def test_conv2d_wavefront_tiles(shape):
     test_conv2d_fwd_and_vjp(shape, False)
 
 
+# few channels (fp32: the kernels that flatten taps and channels into one reduction axis): one pixel, bands of one row and of a
+# whole odd image, a last band with fewer rows, one to 32 outputs, the longest reduction axes, strides, filters not square
+SMALL_SHAPES = [
+    (1, 1, 1, 1, 1, 3, 1, 1), (2, 31, 31, 3, 32, 3, 1, 1), (1, 13, 300, 2, 5, 3, 1, 1), (3, 26, 26, 3, 17, 3, 2, 1),
+    (2, 11, 9, 6, 16, 5, 1, 2), (1, 12, 12, 12, 16, 5, 1, 2), (2, 10, 10, 7, 8, 3, 1, 2), (600, 5, 4, 3, 4, 3, 1, 1),
+    (2, 9, 10, 5, 3, 3, 3, 0), (1, 40, 33, 1, 6, 1, 1, 0, 7),
+]
+
+
+@pytest.mark.parametrize("shape", SMALL_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_conv2d_few_channels(shape):
+    test_conv2d_fwd_and_vjp(shape, False)
+
+
 def _random_conv_shapes(count, seed):
     """Seeded shapes drawn from the values at which the library switches kernels (channel counts around the
     loaders' vector widths and the LDS-patch kernel's 16/24/32/64, image sizes around its 8/16/32-wide tiles,
