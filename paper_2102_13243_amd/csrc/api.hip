@@ -132,10 +132,10 @@ static size_t conv_vjp_ws_parts(const s4tf_conv_desc& d, size_t* dz_bytes) {
 }
 
 int conv_fwd_impl(const s4tf_conv_desc& d, const void* x, const void* w, const float* bias, void* y, hipStream_t st,
-                  float* stats_part, int* stats_rows) {
+                  float* stats_part, StatRuns* runs) {
   ConvGeom g = conv_geom(d);
-  if (stats_rows) *stats_rows = 0;
-  if (d.groups == 1) return igemm_fwd(g, d.dtype, x, w, bias, d.act, y, st, stats_part, stats_rows);
+  if (runs) *runs = StatRuns();
+  if (d.groups == 1) return igemm_fwd(g, d.dtype, x, w, bias, d.act, y, st, stats_part, runs);
   return dwconv_fwd(g, d.dtype, x, w, bias, d.act, y, st);
 }
 // dz: cotangent after the activation pullback

@@ -241,24 +241,28 @@ __global__ __launch_bounds__(FIN_THREADS) void bn_stats_finalize_kernel(const T*
   invstd[c] = (float)(1.0 / sqrt(var + (double)eps));
 }
 
-// Statistics from the partial sums a convolution left behind: run i covers rows [i*rows, min(M, (i+1)*rows))
-// and holds per channel s_i = sum x and q_i = sum (x - s_i/n_i)^2.  With S = sum s_i:
+// Statistics from the partial sums a convolution left behind: run i covers n_i pixels (see StatRuns) and holds per channel s_i = sum x and q_i = sum (x - s_i/n_i)^2.  With S = sum s_i:
 //   mean = S/M,   M*var = sum q_i + sum s_i^2/n_i - S^2/M      (all in double)
 // The table is laid out channel by channel, part[(which*C + c)*runs + i]: the runs of a channel are adjacent,
 // so the 1024/CPB lanes that a block gives each of its CPB channels read whole cache lines (run-major, the
 // table of a 64-channel layer with thousands of runs cost every block a fetch of every line: 31 us for the
 // first layer of a ResNet-50 at batch 64, 10 us for each 56x56 layer).  The lanes of a wavefront are added by
 // a shuffle butterfly, the wavefronts of a channel through LDS, in a fixed order.
+// is run i the last of its period?
+__device__ inline bool last_run(int i, const StatRuns& R) {
+  return R.period == R.count ? i == R.count - 1 : (unsigned)(i + 1) % (unsigned)R.period == 0;
+}
+
 template <int CPB>
-__global__ __launch_bounds__(1024) void bn_stats_from_runs_kernel(const float* __restrict__ part, int runs, int rows,
-                                                                  long long M, int C, float eps, float* __restrict__ mean,
+__global__ __launch_bounds__(1024) void bn_stats_from_runs_kernel(const float* __restrict__ part, StatRuns R, long long M, int C,
+                                                                  float eps, float* __restrict__ mean,
                                                                   float* __restrict__ invstd) {
   constexpr int ZL = 1024 / CPB, WPC = ZL / 64;  // lanes and wavefronts per channel
   static_assert(ZL % 64 == 0, "a wavefront serves one channel");
   __shared__ double sh[16][3];
   const int cl = threadIdx.x / ZL, zl = threadIdx.x % ZL, c = xcd_channel_block() * CPB + cl;
-  const double inv_rows = 1.0 / (double)rows;
-  const double inv_last = 1.0 / (double)(M - (long long)(runs - 1) * rows);
+  const int runs = R.count;
+  const double inv_rows = 1.0 / (double)R.rows, inv_last = 1.0 / (double)R.last;
   double v[3] = {0.0, 0.0, 0.0};
   if (c < C) {
     const float* __restrict__ srow = part + (long long)c * runs;
@@ -269,7 +273,7 @@ __global__ __launch_bounds__(1024) void bn_stats_from_runs_kernel(const float* _
       const double q = (double)qrow[i];
       v[0] += s;
       v[1] += q;
-      v[2] += s * s * (i == runs - 1 ? inv_last : inv_rows);
+      v[2] += s * s * (last_run(i, R) ? inv_last : inv_rows);
     }
   }
   for (int off = 1; off < 64; off <<= 1) {
@@ -598,14 +602,15 @@ Plan make_wide_plan(size_t M, int C, int dtype, int target_blocks) {
 
 // mean and 1/std of the cb <= 64 channels from c0 on, out of a convolution's table (see bn_stats_from_runs_kernel): 16 to
 // 64 lanes per channel, in double
-__device__ inline void stats_of_block(const float* __restrict__ part, int runs, int rows, long long M, int C, float eps, int c0,
+__device__ inline void stats_of_block(const float* __restrict__ part, const StatRuns& R, long long M, int C, float eps, int c0,
                                       int cb, float* mu, float* is) {
   const int lpc = cb <= 16 ? 64 : cb <= 32 ? 32 : 16;  // WIDE / lpc channels at least cb
   const int ch = threadIdx.x / lpc, l = threadIdx.x % lpc, c = c0 + ch;
   double S = 0.0, Q = 0.0, W = 0.0;
   const bool live = ch < cb && c < C;
   if (live) {
-    const double inv_rows = 1.0 / (double)rows, inv_last = 1.0 / (double)(M - (long long)(runs - 1) * rows);
+    const int runs = R.count;
+    const double inv_rows = 1.0 / (double)R.rows, inv_last = 1.0 / (double)R.last;
     const float* __restrict__ srow = part + (long long)c * runs;
     const float* __restrict__ qrow = part + ((long long)C + c) * runs;
 #pragma unroll 8
@@ -613,7 +618,7 @@ __device__ inline void stats_of_block(const float* __restrict__ part, int runs, 
       const double sv = (double)srow[i];
       S += sv;
       Q += (double)qrow[i];
-      W += sv * sv * (i == runs - 1 ? inv_last : inv_rows);
+      W += sv * sv * (last_run(i, R) ? inv_last : inv_rows);
     }
   }
   for (int off = 1; off < lpc; off <<= 1) {
@@ -633,7 +638,7 @@ __device__ inline void stats_of_block(const float* __restrict__ part, int runs, 
 template <typename T, int V>
 __global__ __launch_bounds__(WIDE) void bn_apply_runs_kernel(const T* __restrict__ x, const T* __restrict__ res,
                                                              const float* __restrict__ gamma, const float* __restrict__ beta,
-                                                             const float* __restrict__ part, int runs, int rows, float eps,
+                                                             const float* __restrict__ part, StatRuns R, float eps,
                                                              float* __restrict__ mean, float* __restrict__ invstd,
                                                              T* __restrict__ y, unsigned char* __restrict__ bits, long long M,
                                                              int C, int cvb, long long per, int act) {
@@ -650,7 +655,7 @@ __global__ __launch_bounds__(WIDE) void bn_apply_runs_kernel(const T* __restrict
     if (res) rv[u] = ldp<T, V>(res + m * C + c);
   };
   load_ahead<U>(p0 + pl, p1, pl_count, load);  // on their way while the block adds up its channels' sums
-  stats_of_block(part, runs, rows, M, C, eps, c0, cb, mul, isl);
+  stats_of_block(part, R, M, C, eps, c0, cb, mul, isl);
   if (blockIdx.y == 0 && (int)threadIdx.x < cb) {
     mean[c0 + threadIdx.x] = mul[threadIdx.x];
     invstd[c0 + threadIdx.x] = isl[threadIdx.x];
@@ -1081,7 +1086,7 @@ size_t bn_workspace(size_t M, int C) {
   } while (0)
 
 int bn_fwd(const s4tf_bn_desc& d, const void* x, const void* res, const float* gamma, const float* beta,
-           void* y, float* mean, float* invstd, void* ws, hipStream_t st, const float* stats_part, int stats_rows,
+           void* y, float* mean, float* invstd, void* ws, hipStream_t st, const float* stats_part, StatRuns R,
            unsigned char* maskbits) {
   const long long M = (long long)d.n * d.h * d.w;
   const int C = d.c;
@@ -1090,34 +1095,33 @@ int bn_fwd(const s4tf_bn_desc& d, const void* x, const void* res, const float* g
   float* part = static_cast<float*>(ws);
   int rc;
   const bool vec = C % (d.dtype == S4TF_BF16 ? 8 : 4) == 0;
-  if (stats_part && stats_rows > 0 && vec) {
-    const int runs = (int)((M + stats_rows - 1) / stats_rows);
+  const bool from_runs = stats_part && R.count > 0;
+  if (from_runs && vec) {
     const Plan pw = make_wide_plan((size_t)M, C, d.dtype, 256);
-    if ((size_t)runs * pw.cvb * pw.V * 2 * sizeof(float) <= MERGE_TABLE_BYTES) {
+    if ((size_t)R.count * pw.cvb * pw.V * 2 * sizeof(float) <= MERGE_TABLE_BYTES) {
       ProfScope ps(PC_BN_APPLY, st);
-      WIDE_LAUNCH(bn_apply_runs_kernel, dim3(pw.cblocks, pw.chunks), (const T*)x, (const T*)res, gamma, beta, stats_part, runs,
-                  stats_rows, d.eps, mean, invstd, (T*)y, maskbits, M, C, pw.cvb, pw.per, d.act);
+      WIDE_LAUNCH(bn_apply_runs_kernel, dim3(pw.cblocks, pw.chunks), (const T*)x, (const T*)res, gamma, beta, stats_part, R,
+                  d.eps, mean, invstd, (T*)y, maskbits, M, C, pw.cvb, pw.per, d.act);
       return launch_status("bn_apply_runs");
     }
   }
-  if (!(stats_part && stats_rows > 0) && vec && (size_t)M <= HOLD_PIXELS) {
+  if (!from_runs && vec && (size_t)M <= HOLD_PIXELS) {
     ProfScope ps(PC_BN_APPLY, st);
     WIDE_LAUNCH(bn_fwd_whole_kernel, dim3((C / pa.V + 3) / 4), (const T*)x, (const T*)res, gamma, beta, (T*)y, mean, invstd, maskbits,
                 (int)M, C, d.act, d.eps);
     return launch_status("bn_fwd_whole");
   }
-  if (stats_part && stats_rows > 0) {
+  if (from_runs) {
     ProfScope ps(PC_BN_STATS, st);
-    const int runs = (int)((M + stats_rows - 1) / stats_rows);
     // lanes per channel by the length of its row of the table: 128 up to 512 runs, 512 up to 2048, else 1024
-    if (runs <= 512)
-      hipLaunchKernelGGL(bn_stats_from_runs_kernel<8>, dim3((C + 7) / 8), dim3(1024), 0, st, stats_part, runs, stats_rows, M, C,
+    if (R.count <= 512)
+      hipLaunchKernelGGL(bn_stats_from_runs_kernel<8>, dim3((C + 7) / 8), dim3(1024), 0, st, stats_part, R, M, C,
                          d.eps, mean, invstd);
-    else if (runs <= 2048)
-      hipLaunchKernelGGL(bn_stats_from_runs_kernel<2>, dim3((C + 1) / 2), dim3(1024), 0, st, stats_part, runs, stats_rows, M, C,
+    else if (R.count <= 2048)
+      hipLaunchKernelGGL(bn_stats_from_runs_kernel<2>, dim3((C + 1) / 2), dim3(1024), 0, st, stats_part, R, M, C,
                          d.eps, mean, invstd);
     else
-      hipLaunchKernelGGL(bn_stats_from_runs_kernel<1>, dim3(C), dim3(1024), 0, st, stats_part, runs, stats_rows, M, C,
+      hipLaunchKernelGGL(bn_stats_from_runs_kernel<1>, dim3(C), dim3(1024), 0, st, stats_part, R, M, C,
                          d.eps, mean, invstd);
     if ((rc = launch_status("bn_stats_from_runs")) != S4TF_OK) return rc;
   } else {
@@ -1217,6 +1221,34 @@ int bn_fwd_static(const s4tf_bn_desc& d, const void* x, const void* res, const f
   // every partial sum the finalize kernel reads is written by the statistics kernel of the same call: nothing
   // has to start at zero, and what an earlier call left behind is never read
   return bn_fwd(d, x, res, gamma, beta, y, mean, invstd, ptr, st);
+}
+
+size_t bn_vjp_sums_bytes(const s4tf_bn_desc& d) {
+  const Plan pw = make_wide_plan((size_t)d.n * d.h * d.w, d.c, d.dtype, 256);
+  return (size_t)pw.chunks * 2 * d.c * sizeof(double);
+}
+int bn_vjp_sums(const s4tf_bn_desc& d, const void* x, const void* y, const float* gamma, const float* beta, const float* mean,
+                const float* invstd, const void* dy, double* part, int* chunks, hipStream_t st) {
+  const long long M = (long long)d.n * d.h * d.w;
+  const int C = d.c, mode = beta && d.act != S4TF_ACT_NONE ? MASK_Z : MASK_Y;
+  const Plan pw = make_wide_plan((size_t)M, C, d.dtype, 256);
+  *chunks = pw.chunks;
+  ProfScope ps(PC_BN_VJP_REDUCE, st);
+  WIDE_LAUNCH_MODE(bn_vjp_reduce_wide_kernel, mode, dim3(pw.cblocks, pw.chunks), (const T*)x, (const T*)y, (const T*)dy, mean, invstd,
+                   gamma, beta, part, M, C, pw.cvb, pw.per, d.act);
+  return launch_status("bn_vjp_sums");
+}
+int bn_vjp_from_sums(const s4tf_bn_desc& d, const void* x, const void* y, const float* gamma, const float* beta, const float* mean,
+                     const float* invstd, const void* dy, void* dx, void* dres, float* dgamma, float* dbeta, const double* part,
+                     int chunks, hipStream_t st) {
+  const long long M = (long long)d.n * d.h * d.w;
+  const int C = d.c, mode = beta && d.act != S4TF_ACT_NONE ? MASK_Z : MASK_Y;
+  const Plan pw = make_wide_plan((size_t)M, C, d.dtype, 256);
+  ProfScope ps(PC_BN_VJP_APPLY, st);
+  WIDE_LAUNCH_MODE(bn_vjp_apply_wide_kernel, mode, dim3(pw.cblocks, pw.chunks), (const T*)x, (const T*)y, (const T*)dy, gamma, mean,
+                   invstd, beta, part, chunks, dgamma, dbeta, (T*)dx, (T*)dres, d.accumulate_dx, d.accumulate_dres, M, C, pw.cvb,
+                   pw.per, d.act);
+  return launch_status("bn_vjp_from_sums");
 }
 
 int bn_vjp(const s4tf_bn_desc& d, const void* x, const void* y, const float* gamma, const float* beta, const float* mean,

@@ -868,42 +868,56 @@ void magic_div(int d, uint32_t& magic, int& shift) {
 }
 
 int igemm_fwd(const ConvGeom& g, int dtype, const void* x, const void* w, const float* bias, int act,
-              void* y, hipStream_t st, float* stats_part, int* stats_rows) {
+              void* y, hipStream_t st, float* stats_part, StatRuns* runs) {
   Args a = {};
   a.g = g; a.a = x; a.b = w; a.out = y; a.bias = bias; a.act = act;
   a.Mg = g.N * g.P * g.Q; a.Ng = g.K; a.Kg = g.R * g.S * g.C;
   a.simple = (g.R == 1 && g.S == 1 && g.stride == 1 && g.pad == 0);
   fill_sizes(a, PASS_FWD, dtype);
-  if (stats_rows) *stats_rows = 0;
+  if (runs) *runs = StatRuns();
   ProfScope ps(PC_CONV_FWD, st);
   if (dtype == S4TF_BF16) {
     fill_tiles(a, 128, 128, Cfg<bf16_t>::BK);
-    if (stats_part && stats_rows && !bias && act == S4TF_ACT_NONE && igemm_dma_ok(PASS_FWD, g, a)) {
+    if (stats_part && runs && !bias && act == S4TF_ACT_NONE && igemm_dma_ok(PASS_FWD, g, a)) {
       a.stats = stats_part;
       const int rc = igemm_dma_launch(PASS_FWD, a, 1, st);
-      *stats_rows = a.stats_rows;
+      *runs = equal_runs((size_t)a.Mg, a.stats_rows);
       return rc;
     }
     return launch<bf16_t, PASS_FWD>(a, 1, st);
   }
-  const bool with_stats = stats_part && stats_rows && !bias && act == S4TF_ACT_NONE;
+  const bool with_stats = stats_part && runs && !bias && act == S4TF_ACT_NONE;
+  if (block_conv_ok(g, dtype) && aligned16(x) && aligned16(w) && aligned16(y)) {
+    BlockConv b = {};
+    b.g = g; b.src = static_cast<const float*>(x); b.w = static_cast<const float*>(w); b.out = static_cast<float*>(y);
+    b.bias = bias; b.conv_act = act; b.stats = with_stats ? stats_part : nullptr;
+    if (with_stats) *runs = block_conv_runs(g);
+    return block_conv(b, false, st);
+  }
+  int rows = 0, rc;
   if (patchconv_fwd_ok(g, dtype) && aligned16(x) && aligned16(w) && aligned16(y))  // few channels, 3x3: out of an LDS patch
-    return patchconv_fwd(g, x, w, bias, act, y, with_stats ? stats_part : nullptr, with_stats ? stats_rows : nullptr, st);
-  if (small_conv_ok(PASS_FWD, g, dtype))
-    return small_conv_fwd(g, static_cast<const float*>(x), static_cast<const float*>(w), bias, act, static_cast<float*>(y),
-                          with_stats ? stats_part : nullptr, with_stats ? stats_rows : nullptr, st);
-  if (wave_gemm_ok(PASS_FWD, g, dtype) && aligned16(x) && aligned16(w) && aligned16(y))
-    return wave_gemm_fwd(g, static_cast<const float*>(x), static_cast<const float*>(w), bias, act, static_cast<float*>(y),
-                      with_stats ? stats_part : nullptr, with_stats ? stats_rows : nullptr, st);
-  if (with_stats) *stats_rows = 32;
-  fill_tiles_f32(a, false);
-  if (with_stats) a.stats = stats_part;
-  return launch<float, PASS_FWD>(a, 1, st);
+    rc = patchconv_fwd(g, x, w, bias, act, y, with_stats ? stats_part : nullptr, with_stats ? &rows : nullptr, st);
+  else if (small_conv_ok(PASS_FWD, g, dtype))
+    rc = small_conv_fwd(g, static_cast<const float*>(x), static_cast<const float*>(w), bias, act, static_cast<float*>(y),
+                        with_stats ? stats_part : nullptr, with_stats ? &rows : nullptr, st);
+  else if (wave_gemm_ok(PASS_FWD, g, dtype) && aligned16(x) && aligned16(w) && aligned16(y))
+    rc = wave_gemm_fwd(g, static_cast<const float*>(x), static_cast<const float*>(w), bias, act, static_cast<float*>(y),
+                       with_stats ? stats_part : nullptr, with_stats ? &rows : nullptr, st);
+  else {
+    rows = 32;
+    fill_tiles_f32(a, false);
+    if (with_stats) a.stats = stats_part;
+    rc = launch<float, PASS_FWD>(a, 1, st);
+  }
+  if (with_stats && rows > 0) *runs = equal_runs((size_t)a.Mg, rows);
+  return rc;
 }
 
-size_t igemm_fwd_stats_bytes(const ConvGeom& g) {  // the finest runs any kernel uses are 32 rows
+size_t igemm_fwd_stats_bytes(const ConvGeom& g) {  // the finest runs are 32 rows, except where bands of whole rows are shorter
   const size_t M = (size_t)g.N * g.P * g.Q;
-  return (M + 31) / 32 * 2 * g.K * sizeof(float);
+  size_t runs = (M + 31) / 32;
+  if (block_conv_ok(g, S4TF_F32) && (size_t)block_conv_runs(g).count > runs) runs = (size_t)block_conv_runs(g).count;
+  return runs * 2 * g.K * sizeof(float);
 }
 
 // Can igemm_dgrad add a (masked) tensor other than the old contents of dx?  Only the stride-1 case of the
@@ -922,7 +936,7 @@ bool igemm_dgrad_can_add_other(const ConvGeom& g, int dtype) {
 
 // Can igemm_dgrad multiply its result by an activation's derivative?  For 16-byte aligned operands.
 bool igemm_dgrad_can_mask(const ConvGeom& g, int dtype) {
-  return small_conv_ok(PASS_DGRAD, g, dtype) || (!patchconv_dgrad_ok(g, dtype) && wave_gemm_ok(PASS_DGRAD, g, dtype));
+  return small_conv_ok(PASS_DGRAD, g, dtype) || (!block_conv_ok(g, dtype) && !patchconv_dgrad_ok(g, dtype) && wave_gemm_ok(PASS_DGRAD, g, dtype));
 }
 
 int igemm_dgrad(const ConvGeom& g, int dtype, const void* dy, const void* w, void* dx, int accumulate,
@@ -978,6 +992,12 @@ int igemm_dgrad(const ConvGeom& g, int dtype, const void* dy, const void* w, voi
   if (dtype == S4TF_BF16) {
     fill_tiles(a, 128, 128, Cfg<bf16_t>::BK);
     return launch<bf16_t, PASS_DGRAD>(a, 1, st);
+  }
+  if (block_conv_ok(g, dtype) && aligned16(dy) && aligned16(w) && aligned16(dx)) {
+    BlockConv b = {};
+    b.g = g; b.src = static_cast<const float*>(dy); b.w = static_cast<const float*>(w); b.out = static_cast<float*>(dx);
+    b.accumulate = accumulate;
+    return block_conv(b, true, st);
   }
   if (small_conv_ok(PASS_DGRAD, g, dtype))
     return small_conv_dgrad(g, static_cast<const float*>(dy), static_cast<const float*>(w), static_cast<float*>(dx), accumulate,

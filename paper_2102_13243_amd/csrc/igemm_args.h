@@ -94,6 +94,44 @@ int wave_gemm_wgrad_splits(const ConvGeom& g);
 bool wave_gemm_bias_ok(const ConvGeom& g);
 int wave_gemm_wgrad(const ConvGeom& g, const float* x, const float* dy, float* out, float* db, hipStream_t st);
 
+// fp32 3x3 / stride 1 / padding 1, 16, 32 or 64 channels in and out (blockconv.hip), with the BatchNorms on either side.
+// flip: the input pullback.
+struct BlockConv {
+  ConvGeom g;
+  const float* w;
+  float* out;          // (N, H, W, K)
+  const float* bias;   // forward
+  int conv_act;        // forward
+  int accumulate;      // pullback: out += ...
+  // what is convolved: src itself, or, with a table (part forward, dpart backward), what the BatchNorm in front makes of it:
+  // forward act(BN(src) + src2); backward the cotangent of BN's input, from src, the cotangent of BN's output, and src2, BN's input
+  const float* src;
+  const float* src2;   // forward: residual, optional
+  const float* mask_y; // backward: BN's output, where a residual went into it
+  float* made;         // what was made
+  float* dres;         // backward, optional: cotangent of the residual
+  int acc_dres;
+  const float* gamma; const float* beta;
+  float* mean; float* invstd;    // forward: written; backward: read
+  const float* part;   // forward: sums and squared deviations of src per run
+  const double* dpart; // backward: runs.count rows of (sum dz, sum dz*xhat)
+  StatRuns runs;
+  float eps;
+  int act;
+  float* dgamma; float* dbeta;   // backward
+  // forward, optional: the same table for out (block_conv_runs)
+  float* stats;
+  // backward, optional: the rows of dpart (block_conv_runs) for the BatchNorm whose output's cotangent `out` is:
+  // nz its input, ny its output where a residual went into it
+  double* npart;
+  const float* nz; const float* ny; const float* nmean; const float* ninvstd; const float* ngamma; const float* nbeta;
+  int nact;
+};
+bool block_conv_ok(const ConvGeom& g, int dtype);
+StatRuns block_conv_runs(const ConvGeom& g);
+size_t block_conv_table_bytes(const ConvGeom& g);  // of either table
+int block_conv(const BlockConv& b, bool flip, hipStream_t st);
+
 // fp32, few channels (smallconv.hip)
 bool small_conv_ok(int pass, const ConvGeom& g, int dtype);
 int small_conv_fwd(const ConvGeom& g, const float* x, const float* w, const float* bias, int act, float* y, float* stats,

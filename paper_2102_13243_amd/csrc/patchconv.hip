@@ -1,28 +1,19 @@
-// fp32 3x3 / stride 1 / padding 1 convolution for layers of few channels (16, 32 or 64 in and out, or the 4
-// padded channels of a first layer) on small images (8, 16 or 32 wide): the layers of a CIFAR ResNet.
+// fp32 convolutions with a short reduction axis, multiplied out of LDS in one go: 1x1 / stride 1 layers that reduce over 16,
+// 24, 32 or 64 channels (forward of an expansion layer, input pullback of a projection layer), and the 3x3 / stride 1 /
+// padding 1 first layer of 4 channels in and 16 out.
 //
-// The implicit-GEMM kernel of igemm.hip gathers every k-tile of the im2col matrix from global memory, nine
-// times the input in all, and pays a block barrier per 32 values of k: on a 131072 x 16 x 144 GEMM that is
-// ~20 us, of which the matrix cores need 4.  Here a workgroup owns 128 consecutive output pixels (whole rows
-// of one image, or two whole 8x8 images) and a block of 16 or 32 output channels, brings the pixels' input
-// patch (their rows plus a one-pixel border, zeros outside the image) and its slice of the filter into LDS
-// once, and multiplies out of LDS with no further barrier:
-//   * v_mfma_f32_16x16x4_f32: 16 pixels x 16 outputs, 4 values of k = 4 adjacent channels of one tap, so a
-//     16-channel layer spends nothing on padding; A: lane l = pixel l%16, channel l/16; B: lane l = channel
-//     l/16, output l%16; D: register v of lane l = pixel 4*(l/16) + v, output l%16;
-//   * a wavefront multiplies 32 pixels (two blocks of 16) by all outputs, so one read of a filter fragment
-//     serves two MFMAs and one read of a pixel fragment serves CO/16;
-//   * patch pixels are CI + 4 floats apart and filter rows CO (+16 from 32 outputs up) floats apart, which
-//     spreads the 64 lanes of either fragment read over the 64 LDS banks.
-// The pullback to the input (dgrad) of such a layer is the same convolution of dy with the filter turned by
-// 180 degrees and its channel axes swapped: the same kernel, told to read the filter that way (FLIP).
-// The forward pass can leave the partial sums of a BatchNorm that follows, per run of 32 pixels, exactly as
-// igemm_fwd does.
-// 1x1 / stride 1 layers whose reduction axis is 16, 24, 32 or 64 channels (forward of an expansion layer, input
-// pullback of a projection layer) take the same kernel with a single tap: 128 pixels and a block of 16, 32 or 48
-// output channels per workgroup, one round of loads, a few MFMAs, the stores.  They are bound by the bytes they
-// move; the implicit-GEMM kernel's fixed cost per workgroup (row decomposition, staged k-loop) was most of
-// their time.
+// A workgroup owns 128 consecutive output pixels (for 3x3: whole rows of one image, or whole images) and a block of 16, 32 or
+// 48 output channels, brings the pixels' input patch and its slice of the filter into LDS once, and multiplies with no
+// further barrier:
+//   * v_mfma_f32_16x16x4_f32: 16 pixels x 16 outputs, 4 values of k = 4 adjacent channels of one tap; A: lane l = pixel l%16,
+//     channel l/16; B: lane l = channel l/16, output l%16; D: register v of lane l = pixel 4*(l/16) + v, output l%16;
+//   * a wavefront multiplies 32 pixels (two blocks of 16) by all outputs, so one read of a filter fragment serves two MFMAs
+//     and one read of a pixel fragment serves CO/16;
+//   * patch pixels are CI + 4 floats apart and filter rows CO (+16 from 32 outputs up) floats apart, which spreads the 64
+//     lanes of either fragment read over the 64 LDS banks.
+// The pullback to the input of a 1x1 layer is the same product with the filter transposed (FLIP).  The forward pass can leave
+// the partial sums of a BatchNorm that follows, per run of 32 pixels, as igemm_fwd describes.  These layers are bound by the
+// bytes they move; the implicit-GEMM kernel's fixed cost per workgroup (row decomposition, staged k-loop) was most of their time.
 #include "s4tf_internal.h"
 
 namespace s4tf {
@@ -269,7 +260,6 @@ bool shape_ok(const ConvGeom& g) {
   if (g.R != 3 || g.S != 3 || g.stride != 1 || g.pad != 1 || !tiling(g.N, g.H, g.W, RH, IMGS)) return false;
   return (long long)g.N * g.H * g.W * (g.C > g.K ? g.C : g.K) < (1LL << 31);
 }
-bool channels_ok(int C, int K) { return (C == 16 && K == 16) || (C == 32 && K == 32) || (C == 64 && K == 64); }
 
 PatchArgs make_args(const ConvGeom& g, const void* in, const void* w, void* out, int out_channels) {
   PatchArgs a = {};
@@ -284,11 +274,11 @@ PatchArgs make_args(const ConvGeom& g, const void* in, const void* w, void* out,
 
 bool patchconv_fwd_ok(const ConvGeom& g, int dtype) {
   if (dtype != S4TF_F32) return false;
-  return point_ok(g, g.C, g.K) || (shape_ok(g) && (channels_ok(g.C, g.K) || (g.C == 4 && g.K == 16)));
+  return point_ok(g, g.C, g.K) || (shape_ok(g) && g.C == 4 && g.K == 16);
 }
 bool patchconv_dgrad_ok(const ConvGeom& g, int dtype) {
   if (dtype != S4TF_F32) return false;
-  return point_ok(g, g.K, g.C) || (shape_ok(g) && channels_ok(g.C, g.K));
+  return point_ok(g, g.K, g.C);
 }
 
 // y = act(conv(x, w) + bias); with `stats`, also the BatchNorm partial sums of igemm_fwd, per run of *stats_rows pixels
@@ -299,9 +289,6 @@ int patchconv_fwd(const ConvGeom& g, const void* x, const void* w, const float* 
   a.bias = bias; a.stats = stats; a.act = act;
   if (stats_rows) *stats_rows = 32;
   if (g.R == 1) return launch_point<false>(g.C, a, st);
-  if (g.C == 16) return launch_patch<16, 16, false>(a, st);
-  if (g.C == 32) return launch_patch<32, 32, false>(a, st);
-  if (g.C == 64) return launch_patch<64, 16, false>(a, st);  // four workgroups of 16 output channels per tile
   return launch_patch<4, 16, false>(a, st);
 }
 
@@ -310,10 +297,7 @@ int patchconv_dgrad(const ConvGeom& g, const void* dy, const void* w, void* dx, 
   if (!aligned16(dy) || !aligned16(w) || !aligned16(dx)) return fail(S4TF_ERR_SHAPE, "patchconv: operands must be 16-byte aligned");
   PatchArgs a = make_args(g, dy, w, dx, g.C);
   a.accumulate = accumulate;
-  if (g.R == 1) return launch_point<true>(g.K, a, st);
-  if (g.C == 16) return launch_patch<16, 16, true>(a, st);
-  if (g.C == 32) return launch_patch<32, 32, true>(a, st);
-  return launch_patch<64, 16, true>(a, st);
+  return launch_point<true>(g.K, a, st);
 }
 
 }  // namespace s4tf

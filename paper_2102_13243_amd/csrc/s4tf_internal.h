@@ -83,16 +83,28 @@ inline ConvGeom conv_geom(const s4tf_conv_desc& d) {
   return g;
 }
 
+// Runs of output pixels that a convolution leaves BatchNorm partial sums for: `count` of them, `rows` pixels each, except that
+// every period-th has `last` (the last band of an image; period == count: the last run of all).
+struct StatRuns {
+  int count = 0, rows = 0, period = 1, last = 0;
+};
+inline StatRuns equal_runs(size_t M, int rows) {
+  StatRuns r;
+  r.rows = rows;
+  r.count = r.period = (int)((M + rows - 1) / rows);
+  r.last = (int)(M - (size_t)(r.count - 1) * rows);
+  return r;
+}
+
 // dense (groups == 1) convolution as implicit GEMM on MFMA
 // stats_part (optional, with bias == NULL and act == none): the kernel also writes, for every run of
-// *stats_rows consecutive output rows (pixels) r and every channel, the sum of the stored outputs and the
+// consecutive output rows (pixels) r (see StatRuns) and every channel, the sum of the stored outputs and the
 // sum of their squared deviations from that run's own mean, channel-major: stats_part[k*runs + r] and
-// stats_part[(K + k)*runs + r] with runs = ceil(N*P*Q / *stats_rows).  *stats_rows comes back 0 when the kernel that ran does not do this.
+// stats_part[(K + k)*runs + r] with runs = runs->count, which comes back 0 when the kernel that ran does not do this.
 int igemm_fwd(const ConvGeom& g, int dtype, const void* x, const void* w, const float* bias, int act,
-              void* y, hipStream_t st, float* stats_part = nullptr, int* stats_rows = nullptr);
+              void* y, hipStream_t st, float* stats_part = nullptr, StatRuns* runs = nullptr);
 size_t igemm_fwd_stats_bytes(const ConvGeom& g);  // upper bound on the size of stats_part
-// fp32 3x3 / stride 1 / padding 1 layers of 16 or 32 channels (and 4 -> 16) whose images are 16 or 32 wide: a
-// kernel that multiplies out of an LDS patch (patchconv.hip); igemm_fwd and igemm_dgrad hand such shapes over
+// fp32 layers with a short reduction axis (patchconv.hip); igemm_fwd and igemm_dgrad hand such shapes over
 bool patchconv_fwd_ok(const ConvGeom& g, int dtype);
 bool patchconv_dgrad_ok(const ConvGeom& g, int dtype);
 int patchconv_fwd(const ConvGeom& g, const void* x, const void* w, const float* bias, int act, void* y, float* stats,
@@ -142,14 +154,14 @@ int unfold2_filter_grad(const float* dwf, float* dw, int R, int S, int C, int K,
 // batch norm
 size_t bn_workspace(size_t M, int C);
 size_t bn_mask_bytes(size_t M, int C, int dtype);
-// stats_part / stats_rows: per-channel partial sums that the producing convolution left (see igemm_fwd);
+// stats_part / runs: per-channel partial sums that the producing convolution left (see igemm_fwd);
 // NULL / 0: the statistics are computed here from x.
 // maskbits (optional, bn_mask_bytes bytes): the forward pass leaves act'(y) there, one bit per output, and a
 // pullback that is given them reads these instead of y (a BatchNorm with a residual cannot rebuild its
 // activation mask from x; the bits are a sixteenth of y in bf16).
 int bn_fwd(const s4tf_bn_desc& d, const void* x, const void* res, const float* gamma, const float* beta,
            void* y, float* mean, float* invstd, void* ws, hipStream_t st, const float* stats_part = nullptr,
-           int stats_rows = 0, unsigned char* maskbits = nullptr);
+           StatRuns runs = StatRuns(), unsigned char* maskbits = nullptr);
 // inference mode: running statistics instead of batch statistics; their update from a training-mode forward
 // pass; folding of an inference-mode BatchNorm into the convolution in front of it
 int bn_inference_fwd(const s4tf_bn_desc& d, const void* x, const void* res, const float* gamma, const float* beta,
@@ -167,6 +179,14 @@ int bn_fwd_static(const s4tf_bn_desc& d, const void* x, const void* res, const f
 int bn_vjp(const s4tf_bn_desc& d, const void* x, const void* y, const float* gamma, const float* beta, const float* mean,
            const float* invstd, const void* dy, void* dx, void* dres, float* dgamma, float* dbeta,
            void* ws, hipStream_t st, const unsigned char* maskbits = nullptr);
+// the two halves of bn_vjp for a channel count that the vectors divide: the sums of dz and dz*xhat as `chunks` rows of
+// [2][C] doubles, and dx, dres, dgamma, dbeta from such rows, whoever left them
+size_t bn_vjp_sums_bytes(const s4tf_bn_desc& d);
+int bn_vjp_sums(const s4tf_bn_desc& d, const void* x, const void* y, const float* gamma, const float* beta, const float* mean,
+                const float* invstd, const void* dy, double* part, int* chunks, hipStream_t st);
+int bn_vjp_from_sums(const s4tf_bn_desc& d, const void* x, const void* y, const float* gamma, const float* beta, const float* mean,
+                     const float* invstd, const void* dy, void* dx, void* dres, float* dgamma, float* dbeta, const double* part,
+                     int chunks, hipStream_t st);
 
 // pools
 // idx (optional, max pool with a channel count that the 16-byte kernels take: pool_saves_positions): one byte per
@@ -217,7 +237,7 @@ int check_ws(const void* ws, size_t have, size_t want);
 
 // a convolution's three passes, dense or depthwise by the descriptor's groups (api.hip)
 int conv_fwd_impl(const s4tf_conv_desc& d, const void* x, const void* w, const float* bias, void* y, hipStream_t st,
-                  float* stats_part = nullptr, int* stats_rows = nullptr);
+                  float* stats_part = nullptr, StatRuns* runs = nullptr);
 int conv_dgrad_impl(const s4tf_conv_desc& d, const void* w, const void* dz, void* dx, hipStream_t st,
                     const void* acc_src = nullptr, const unsigned char* acc_bits = nullptr, const void* mask = nullptr,
                     int mask_act = S4TF_ACT_NONE);

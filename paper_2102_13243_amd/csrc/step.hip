@@ -79,6 +79,12 @@ struct NetPlan {
   // BatchNorm need not write its residual cotangent dz = act'(y) dy: the convolution's dgrad adds it from dy
   // and the bits in its epilogue (same values, one tensor less written).
   std::vector<int> defer_conv;
+  // BatchNorms inside the launches of the 3x3 convolutions around them (blockconv.hip), per BatchNorm op of the main branch:
+  // apply_in: the convolution right behind makes this BatchNorm's output while it loads; sums_in: that convolution's input
+  // pullback takes the sums that this BatchNorm's pullback needs; vjp_in: the input pullback of the convolution right in
+  // front makes this BatchNorm's input cotangent while it loads
+  std::vector<char> apply_in, sums_in, vjp_in;
+  size_t table_off[2], table_bytes;  // partial sums handed from launch to launch on the main branch, in turn
   std::vector<char> masked;  // per convolution: its consumer's pullback multiplies by the activation's derivative
   std::vector<size_t> mask_off;      // per op: activation bits of a BatchNorm with residual and activation (0: none)
   std::vector<size_t> stat_off;      // per op: save_mean/invstd (BN); max pool: the saved window positions (one byte per output)
@@ -139,13 +145,16 @@ int plan_net(const s4tf_net_desc* net, NetPlan& pl) {
   pl.mask_off.assign(nops, 0);
   pl.defer_conv.assign(nops, -1);
   pl.masked.assign(nops, 0);
+  pl.apply_in.assign(nops, 0);
+  pl.sums_in.assign(nops, 0);
+  pl.vjp_in.assign(nops, 0);
   pl.pad_c.assign(nops, 0);
   pl.fold.assign(nops, 0);
   pl.xpad_off.assign(nops, 0);
   pl.wpad_off.assign(nops, 0);
   pl.dwpad_off.assign(nops, 0);
   pl.t[0] = TensorPlan{net->n, net->h, net->w, net->c, (size_t)net->n * net->h * net->w * net->c, 0, 0, 0, -1, 0};
-  size_t pcount = 0, off = 0, scratch = 0, wscratch = 0;
+  size_t pcount = 0, off = 0, scratch = 0, wscratch = 0, table = 0;
   auto add_param = [&](int op, int slot, size_t n) {
     pl.poff[2 * op + slot] = (int64_t)pcount;
     pl.psize[2 * op + slot] = (int64_t)n;
@@ -198,6 +207,7 @@ int plan_net(const s4tf_net_desc* net, NetPlan& pl) {
           if (net->ops[k].kind == S4TF_OP_BN && net->ops[k].in == i + 1) {
             ws = igemm_fwd_stats_bytes(g);
             if (ws > scratch) scratch = ws;
+            if (ws > table) table = ws;
           }
         break;
       }
@@ -325,7 +335,7 @@ int plan_net(const s4tf_net_desc* net, NetPlan& pl) {
   pl.wscratch_bytes = align_up(wscratch, 256);
   pl.sscratch_off = pl.wscratch_off + pl.wscratch_bytes;
   pl.head_off = pl.sscratch_off + pl.scratch_bytes;
-  pl.total_bytes = pl.head_off + align_up(pl.head_bytes, 256);
+  size_t end = pl.head_off + align_up(pl.head_bytes, 256);
   // side branches
   pl.branch_of.assign(nops, -1);
   pl.start_after.assign(nops, -1);
@@ -348,6 +358,41 @@ int plan_net(const s4tf_net_desc* net, NetPlan& pl) {
     pl.start_after[X - 1] = id;
     pl.needs[user] = id;
   }
+  // BatchNorms inside the 3x3 convolutions around them
+  auto block_of = [&](int i, ConvGeom& g) {  // op i is such a convolution on the main branch
+    const s4tf_op& op = net->ops[i];
+    if (op.kind != S4TF_OP_CONV || op.groups != 1 || pl.branch_of[i] >= 0 || pl.t[op.in].root == 0) return false;
+    const TensorPlan& in = pl.t[op.in];
+    const s4tf_conv_desc d = {in.n, in.h, in.w, in.c, op.k, op.r, op.s, op.stride, op.pad, op.groups, net->dtype, op.act, 0};
+    g = conv_geom(d);
+    return block_conv_ok(g, net->dtype);
+  };
+  for (int j = 1; j + 1 < nops; ++j) {
+    const s4tf_op& bn = net->ops[j];
+    if (bn.kind != S4TF_OP_BN || pl.branch_of[j] >= 0 || pl.t[j + 1].root != j + 1) continue;
+    ConvGeom g;
+    const bool before = bn.in == j && pl.t[j].root == j && net->ops[j - 1].act == S4TF_ACT_NONE && block_of(j - 1, g);
+    if (before) {
+      // (its own input cotangent and the residual's may not be one tensor: the launch reads and writes both)
+      const int rsrc = bn.res >= 0 ? pl.t[bn.res].root : -1;
+      pl.vjp_in[j] = rsrc != pl.t[net->ops[j - 1].in].root;
+      if (block_conv_table_bytes(g) > table) table = block_conv_table_bytes(g);
+    }
+    if (net->ops[j + 1].in == j + 1 && block_of(j + 1, g)) {
+      // no launch but the convolution's may need the output before: no side branch starts from it
+      pl.apply_in[j] = pl.start_after[j] < 0 && !pl.mask_off[j];
+      pl.sums_in[j] = 1;
+      if (block_conv_table_bytes(g) > table) table = block_conv_table_bytes(g);
+    }
+    if (pl.vjp_in[j] && !pl.sums_in[j]) {
+      const TensorPlan& in = pl.t[bn.in];
+      const s4tf_bn_desc d = {in.n, in.h, in.w, in.c, bn.eps, bn.act, net->dtype, 0};
+      if (bn_vjp_sums_bytes(d) > table) table = bn_vjp_sums_bytes(d);
+    }
+  }
+  pl.table_bytes = align_up(table, 256);
+  for (int k = 0; k < 2; ++k) { pl.table_off[k] = end; end += pl.table_bytes; }
+  pl.total_bytes = end;
   // identity shortcuts whose residual cotangent the consuming convolution's dgrad can add by itself
   for (int i = 0; i < nops; ++i) {
     const s4tf_op& bn = net->ops[i];
@@ -375,15 +420,22 @@ int plan_net(const s4tf_net_desc* net, NetPlan& pl) {
 enum CmdKind : uint8_t {
   K_FORK, K_JOIN, K_SIDE_DONE, K_WAIT_SIDE,        // stream operations (a: event slot)
   K_CONV_FWD, K_BN_FWD, K_POOL_FWD, K_HEAD, K_HEAD_PARAMS,  // forward (conv: a = 1 when it emits statistics partial
-                                                   //  sums; head: b = 1 when its parameter gradients follow at once)
+                                                   //  sums, b = BatchNorm it applies while it loads, or -1; head: b = 1
+                                                   //  when its parameter gradients follow at once)
+  K_BLOCK_DGRAD,  // dgrad with BatchNorms: a = accumulate, b = the one behind or -1, c = the one in front or -1, d = acc_dres
+  K_BN_SUMS,      // the sums of a BatchNorm's pullback
+  K_BN_VJP_SUMS,  // the rest of it (a, b as for K_BN_VJP)
   K_ACT_VJP, K_DGRAD, K_PARAM_GRADS, K_BN_VJP,     // pullbacks (dgrad: a = accumulate, b = BatchNorm whose residual
   K_POOL_VJP, K_SGD                                //  cotangent it adds or -1; bn: a = accumulate into dres, b = 1 when
 };                                                 //  dres is left to that dgrad; pool: a = accumulate; sgd: a = part)
+// Partial sums up to this size are added up by every workgroup of a convolution that applies the BatchNorm itself
+constexpr size_t BLOCK_TABLE_BYTES = 128 << 10;
+
 struct Cmd {
   uint8_t kind;
   uint8_t side;  // 1: the library's second stream, 0: the caller's
   uint8_t scr;   // 1: the side branches' scratch, 0: the main scratch
-  int op, a, b;
+  int op, a, b, c, d;
 };
 
 }  // namespace
@@ -410,8 +462,8 @@ int record_schedule(s4tf_net& N) {
   out.clear();
   const int nops = net->n_ops;
   const bool one_stream = pl.one_stream;
-  auto emit = [&](uint8_t kind, bool side, bool scr, int op, int a = 0, int b = -1) {
-    out.push_back(Cmd{kind, (uint8_t)((side && !one_stream) ? 1 : 0), (uint8_t)(scr ? 1 : 0), op, a, b});
+  auto emit = [&](uint8_t kind, bool side, bool scr, int op, int a = 0, int b = -1, int c = -1, int d = 0) {
+    out.push_back(Cmd{kind, (uint8_t)((side && !one_stream) ? 1 : 0), (uint8_t)(scr ? 1 : 0), op, a, b, c, d});
   };
   auto resolve = [&](int t) -> int { return pl.t[t].root; };
   // side -> main dependencies: the event slot a side branch's output (forward) or a tensor's cotangent
@@ -446,10 +498,12 @@ int record_schedule(s4tf_net& N) {
           if (net->ops[k].kind == S4TF_OP_BN && net->ops[k].in == i + 1) { bn_next = true; break; }
           if (pl.branch_of[k] < 0 || pl.branch_of[i] >= 0) break;
         }
-        emit(K_CONV_FWD, side, side, i, bn_next ? 1 : 0);
+        emit(K_CONV_FWD, side, side, i, bn_next ? 1 : 0, i > 0 && pl.apply_in[i - 1] ? i - 1 : -1);
         break;
       }
-      case S4TF_OP_BN: emit(K_BN_FWD, side, side, i); break;
+      case S4TF_OP_BN:
+        if (!pl.apply_in[i]) emit(K_BN_FWD, side, side, i);
+        break;
       case S4TF_OP_AVGPOOL2:
       case S4TF_OP_MAXPOOL3S2: emit(K_POOL_FWD, side, side, i); break;
       default: break;  // flatten: a reinterpretation
@@ -487,6 +541,7 @@ int record_schedule(s4tf_net& N) {
   // FORK_EVERY convolutions at a time: cotangent buffers are never reused, so a filter gradient can start any
   // time after its convolution's output cotangent is final.
   constexpr int FORK_EVERY = 3;
+  int block_acc_dres = 0;
   std::vector<int> pending;
   std::vector<int> convs_before(nops, 0);  // main-branch convolutions with a smaller op index
   for (int k = 1; k < nops; ++k)
@@ -530,6 +585,10 @@ int record_schedule(s4tf_net& N) {
           emit(K_DGRAD, on_side, on_side, i, 0, b);
           deferred[src] = -1;
           written[src] = 1;
+        } else if (want_dx && !pl.pad_c[i] && (pl.vjp_in[i + 1] || (i > 0 && pl.sums_in[i - 1]))) {
+          emit(K_BLOCK_DGRAD, on_side, on_side, i, written[src] ? 1 : 0, pl.vjp_in[i + 1] ? i + 1 : -1, i > 0 && pl.sums_in[i - 1] ? i - 1 : -1,
+               block_acc_dres);
+          written[src] = 1;
         } else if (want_dx && !pl.pad_c[i]) {
           emit(K_DGRAD, on_side, on_side, i, written[src] ? 1 : 0, -1);
           written[src] = 1;
@@ -561,7 +620,12 @@ int record_schedule(s4tf_net& N) {
           deferred[rsrc] = i;
           leave_dres = 1;
         }
-        emit(K_BN_VJP, on_side, on_side, i, acc_dres, leave_dres);
+        if (pl.vjp_in[i]) {  // the dgrad of the convolution in front does the rest
+          if (!pl.sums_in[i]) emit(K_BN_SUMS, false, false, i);
+          block_acc_dres = acc_dres;
+        } else {
+          emit(pl.sums_in[i] ? K_BN_VJP_SUMS : K_BN_VJP, on_side, on_side, i, acc_dres, leave_dres);
+        }
         written[src] = 1;
         if (rsrc > 0 && !leave_dres) written[rsrc] = 1;
         break;
@@ -714,7 +778,10 @@ int run_step(const s4tf_net& N, s4tf_params* params, const s4tf_batch* batch, fl
   };
   void* scratch_of[2] = {ws + pl.scratch_off, ws + pl.sscratch_off};
   void* wscratch = ws + pl.wscratch_off;
-  int stats_rows[2] = {0, 0};  // per scratch: > 0 when the op before, a convolution, left partial statistics there
+  StatRuns runs[2];            // per scratch: the partial statistics that the op before, a convolution, left
+  int turn = 0, chunks = 0;    // main branch: the table written last, and the rows of pullback sums in it
+  auto table = [&](int k) -> void* { return ws + pl.table_off[k]; };
+  auto bn_stats = [&](int j) -> float* { return reinterpret_cast<float*>(ws + pl.stat_off[j]); };
 
   for (const Cmd& c : N.cmds) {
     const hipStream_t s = c.side ? side->stream : st;
@@ -738,11 +805,36 @@ int run_step(const s4tf_net& N, s4tf_params* params, const s4tf_batch* batch, fl
       case K_CONV_FWD: {
         const s4tf_op& op = net->ops[i];
         const TensorPlan& in = pl.t[op.in];
-        stats_rows[c.scr] = 0;
+        const StatRuns prev = runs[c.scr];
+        runs[c.scr] = StatRuns();
         s4tf_conv_desc d = conv_desc(i, 0);
         const float* bias = op.has_bias ? params->master + pl.poff[2 * i + 1] : nullptr;
-        float* sp = c.a ? static_cast<float*>(scr) : nullptr;
-        int* sr = c.a ? &stats_rows[c.scr] : nullptr;
+        const float* given = static_cast<const float*>(table(turn));
+        float* sp = !c.a ? nullptr : static_cast<float*>(c.scr ? scr : table(turn ^= 1));
+        StatRuns* sr = c.a ? &runs[c.scr] : nullptr;
+        if (c.b >= 0) {
+          const s4tf_op& bn = net->ops[c.b];
+          const void* res = bn.res >= 0 ? act_ptr(bn.res) : nullptr;
+          const float* gamma = params->master + pl.poff[2 * c.b];
+          const float* beta = params->master + pl.poff[2 * c.b + 1];
+          if (prev.count > 0 && (size_t)prev.count * in.c * 2 * sizeof(float) <= BLOCK_TABLE_BYTES) {
+            BlockConv b = {};
+            b.g = conv_geom(d);
+            b.w = static_cast<const float*>(conv_w(i)); b.out = static_cast<float*>(out_ptr(i + 1)); b.bias = bias; b.conv_act = op.act;
+            b.src = static_cast<const float*>(act_ptr(bn.in)); b.src2 = static_cast<const float*>(res); b.made = static_cast<float*>(out_ptr(c.b + 1));
+            b.gamma = gamma; b.beta = beta; b.mean = bn_stats(c.b); b.invstd = bn_stats(c.b) + in.c;
+            b.part = given; b.runs = prev; b.eps = bn.eps; b.act = bn.act;
+            if (c.a && !bias && op.act == S4TF_ACT_NONE) {
+              b.stats = sp;
+              *sr = block_conv_runs(b.g);
+            }
+            CHECK(block_conv(b, false, s));
+            break;
+          }
+          s4tf_bn_desc bd = {in.n, in.h, in.w, in.c, bn.eps, bn.act, dt, 0};
+          CHECK(bn_fwd(bd, act_ptr(bn.in), res, gamma, beta, out_ptr(c.b + 1), bn_stats(c.b), bn_stats(c.b) + in.c, scr, s,
+                       prev.count > 0 ? given : nullptr, prev));
+        }
         if (pl.fold[i]) {
           CHECK(fold2_pixels(act_ptr(op.in), ws + pl.xpad_off[i], in.n, in.h, in.w, in.c, op.pad, s));
           CHECK(fold2_filter(conv_w(i), ws + pl.wpad_off[i], op.r, op.s, in.c, op.k, s));
@@ -762,20 +854,20 @@ int run_step(const s4tf_net& N, s4tf_params* params, const s4tf_batch* batch, fl
       case K_BN_FWD: {
         const s4tf_op& op = net->ops[i];
         const TensorPlan& in = pl.t[op.in];
-        const int prev_rows = stats_rows[c.scr];
-        stats_rows[c.scr] = 0;
+        const StatRuns prev = runs[c.scr];
+        runs[c.scr] = StatRuns();
         s4tf_bn_desc d = {in.n, in.h, in.w, in.c, op.eps, op.act, dt, 0};
-        float* stats = reinterpret_cast<float*>(ws + pl.stat_off[i]);
+        float* stats = bn_stats(i);
         CHECK(bn_fwd(d, act_ptr(op.in), op.res >= 0 ? act_ptr(op.res) : nullptr, params->master + pl.poff[2 * i],
                      params->master + pl.poff[2 * i + 1], out_ptr(i + 1), stats, stats + in.c, scr, s,
-                     prev_rows > 0 ? static_cast<const float*>(scr) : nullptr, prev_rows,
+                     prev.count > 0 ? static_cast<const float*>(c.scr ? scr : table(turn)) : nullptr, prev,
                      pl.mask_off[i] ? reinterpret_cast<unsigned char*>(ws + pl.mask_off[i]) : nullptr));
         break;
       }
       case K_POOL_FWD: {
         const s4tf_op& op = net->ops[i];
         const TensorPlan& in = pl.t[op.in];
-        stats_rows[c.scr] = 0;
+        runs[c.scr] = StatRuns();
         s4tf_pool_desc d = {in.n, in.h, in.w, in.c, op.kind == S4TF_OP_AVGPOOL2 ? S4TF_POOL_AVG2 : S4TF_POOL_MAX3S2, dt, 0};
         unsigned char* pos = pool_saves_positions(d) ? reinterpret_cast<unsigned char*>(ws + pl.stat_off[i]) : nullptr;
         CHECK(pool_fwd(d, act_ptr(op.in), out_ptr(i + 1), s, pos));
@@ -814,6 +906,37 @@ int run_step(const s4tf_net& N, s4tf_params* params, const s4tf_batch* batch, fl
                                 masking(src)));
         break;
       }
+      case K_BLOCK_DGRAD: {
+        const s4tf_op& op = net->ops[i];
+        const TensorPlan& in = pl.t[op.in];
+        BlockConv b = {};
+        b.g = conv_geom(conv_desc(i, c.a));
+        b.w = static_cast<const float*>(conv_w(i)); b.out = static_cast<float*>(grad_ptr(in.root)); b.accumulate = c.a;
+        b.src = static_cast<const float*>(grad_ptr(i + 1));
+        if (c.b >= 0) {  // the BatchNorm behind: its output's cotangent in, its input's made
+          const s4tf_op& bn = net->ops[c.b];
+          const int rsrc = bn.res >= 0 ? pl.t[bn.res].root : -1;
+          b.made = static_cast<float*>(grad_ptr(i + 1));
+          b.src = static_cast<const float*>(grad_ptr(c.b + 1)); b.src2 = static_cast<const float*>(act_ptr(i + 1));
+          b.mask_y = bn.res >= 0 ? static_cast<const float*>(act_ptr(c.b + 1)) : nullptr;
+          b.dres = rsrc > 0 ? static_cast<float*>(grad_ptr(rsrc)) : nullptr; b.acc_dres = c.d;
+          b.gamma = params->master + pl.poff[2 * c.b]; b.beta = params->master + pl.poff[2 * c.b + 1];
+          b.mean = bn_stats(c.b); b.invstd = bn_stats(c.b) + op.k;
+          b.dpart = static_cast<const double*>(table(turn)); b.runs.count = chunks; b.act = bn.act;
+          b.dgamma = params->grad + pl.poff[2 * c.b]; b.dbeta = params->grad + pl.poff[2 * c.b + 1];
+        }
+        if (c.c >= 0) {  // the BatchNorm in front: `out` is its output's cotangent
+          const s4tf_op& bn = net->ops[c.c];
+          b.npart = static_cast<double*>(table(turn ^= 1));
+          chunks = block_conv_runs(b.g).count;
+          b.nz = static_cast<const float*>(act_ptr(bn.in)); b.ny = bn.res >= 0 ? static_cast<const float*>(act_ptr(c.c + 1)) : nullptr;
+          b.nmean = bn_stats(c.c); b.ninvstd = bn_stats(c.c) + in.c;
+          b.ngamma = params->master + pl.poff[2 * c.c]; b.nbeta = params->master + pl.poff[2 * c.c + 1];
+          b.nact = bn.act;
+        }
+        CHECK(block_conv(b, true, s));
+        break;
+      }
       case K_PARAM_GRADS: {  // filter (and bias) gradient of convolution i
         const s4tf_op& cv = net->ops[i];
         const TensorPlan& cin = pl.t[cv.in];
@@ -837,6 +960,8 @@ int run_step(const s4tf_net& N, s4tf_params* params, const s4tf_batch* batch, fl
                                     pl.wscratch_bytes, s));
         break;
       }
+      case K_BN_SUMS:
+      case K_BN_VJP_SUMS:
       case K_BN_VJP: {
         const s4tf_op& op = net->ops[i];
         const TensorPlan& in = pl.t[op.in];
@@ -847,6 +972,17 @@ int run_step(const s4tf_net& N, s4tf_params* params, const s4tf_batch* batch, fl
         void* dres = (rsrc > 0 && c.b != 1) ? grad_ptr(rsrc) : nullptr;
         // no residual in the forward pass: the pullback rebuilds the activation mask from x and skips y
         const float* beta = op.res < 0 ? params->master + pl.poff[2 * i + 1] : nullptr;
+        if (c.kind == K_BN_SUMS) {
+          CHECK(bn_vjp_sums(d, act_ptr(src), out_ptr(i + 1), params->master + pl.poff[2 * i], beta, stats, stats + in.c, grad_ptr(i + 1),
+                            static_cast<double*>(table(turn ^= 1)), &chunks, s));
+          break;
+        }
+        if (c.kind == K_BN_VJP_SUMS) {
+          CHECK(bn_vjp_from_sums(d, act_ptr(src), out_ptr(i + 1), params->master + pl.poff[2 * i], beta, stats, stats + in.c,
+                                 grad_ptr(i + 1), grad_ptr(src), dres, params->grad + pl.poff[2 * i], params->grad + pl.poff[2 * i + 1],
+                                 static_cast<const double*>(table(turn)), chunks, s));
+          break;
+        }
         CHECK(bn_vjp(d, act_ptr(src), out_ptr(i + 1), params->master + pl.poff[2 * i], beta, stats, stats + in.c,
                      grad_ptr(i + 1), grad_ptr(src), dres, params->grad + pl.poff[2 * i], params->grad + pl.poff[2 * i + 1], scr, s,
                      pl.mask_off[i] ? reinterpret_cast<const unsigned char*>(ws + pl.mask_off[i]) : nullptr));

@@ -206,6 +206,19 @@ def test_conv2d_few_channels(shape):
     test_conv2d_fwd_and_vjp(shape, False)
 
 
+# fp32 3x3 layers of 16, 32 or 64 channels at the edges of the band kernel: one row, one column, a last band with fewer rows,
+# images wider than a wavefront's pixels, one wavefront, several workgroups per image and per block of outputs
+BLOCK_SHAPES = [
+    (1, 1, 1, 16, 16, 3, 1, 1), (2, 13, 31, 16, 16, 3, 1, 1), (3, 1, 70, 32, 32, 3, 1, 1), (1, 31, 1, 64, 64, 3, 1, 1),
+    (2, 62, 62, 16, 16, 3, 1, 1), (5, 23, 9, 32, 32, 3, 1, 1), (2, 20, 40, 64, 64, 3, 1, 1), (300, 3, 3, 64, 64, 3, 1, 1),
+]
+
+
+@pytest.mark.parametrize("shape", BLOCK_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_conv2d_bands(shape):
+    test_conv2d_fwd_and_vjp(shape, False)
+
+
 def _random_conv_shapes(count, seed):
     """Seeded shapes drawn from the values at which the library switches kernels (channel counts around the
     loaders' vector widths and the LDS-patch kernel's 16/24/32/64, image sizes around its 8/16/32-wide tiles,
@@ -745,6 +758,27 @@ RANDOM_NET_SEEDS = [0, 1, 2, 3, 5, 6, 7, 8]   # (seed 4: two entries of a max-po
 @pytest.mark.parametrize("seed", RANDOM_NET_SEEDS)
 def test_train_step_seeded_random_nets_fp32(seed):
     net = _random_net(seed)
+    wl = kink_free_workload(net, True)
+    ref = orc.train_step(net, wl["x"], wl["labels"], wl["params"], keep_cotangents=True)
+    gpu = run_gpu_steps(net, wl, local=True)
+    compare_step_strict(net, wl, gpu, ref)
+
+
+@pytest.mark.parametrize("hw,c,acts", [(13, 16, ("relu", "relu")), (10, 32, ("relu6", "none")), (6, 64, ("none", "relu6"))])
+def test_train_step_batchnorms_inside_convolutions(hw, c, acts):
+    """3x3 layers whose BatchNorms run inside their launches: behind another such layer and behind one that is not, with a
+    residual over two layers and over one (whose cotangent is then the layer's own input's), with and without activation."""
+    b = nets._Builder()
+    t = b.add(nets._bn(b.add(nets._conv(0, c, 3, pad=1)), "relu"))
+    u = b.add(nets._bn(b.add(nets._conv(t, c, 3, pad=1)), acts[0]))
+    t = b.add(nets._bn(b.add(nets._conv(u, c, 3, pad=1)), acts[1], res=t))
+    t = b.add(nets._bn(b.add(nets._conv(t, c, 3, pad=1)), acts[1], res=t))
+    t = b.add(nets._bn(b.add(nets._conv(t, c, 1)), "relu"))
+    t = b.add(nets._bn(b.add(nets._conv(t, c, 3, pad=1, act=acts[0])), acts[1]))
+    t = b.add(nets._bn(b.add(nets._conv(t, c, 3, pad=1, bias=True)), acts[1]))
+    b.add({"kind": "head", "in": t, "classes": 5})
+    net = dict(name="bands", dtype="f32", input=(3, hw, hw, 3), classes=5, lr=0.1, momentum=0.9, seed=7100 + hw, init="he",
+               x_dist="normal", ops=b.ops)
     wl = kink_free_workload(net, True)
     ref = orc.train_step(net, wl["x"], wl["labels"], wl["params"], keep_cotangents=True)
     gpu = run_gpu_steps(net, wl, local=True)
