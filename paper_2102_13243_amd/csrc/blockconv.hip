@@ -275,6 +275,7 @@ __global__ __launch_bounds__(1024) void block_conv_kernel(const BlockArgs a) {
     }
     const float lo = b.act != S4TF_ACT_NONE ? 0.f : -__builtin_inff(), hi = b.act == S4TF_ACT_RELU6 ? 6.f : __builtin_inff();
     float* __restrict__ made = b.made ? b.made + img * C : nullptr;
+    const bool no_act = b.act == S4TF_ACT_NONE;
     float* dres = FLIP && b.dres ? b.dres + img * C : nullptr;
     for (int i0 = tid; i0 < chunks; i0 += U * T) {
       if (i0 != tid) load(i0);
@@ -292,7 +293,7 @@ __global__ __launch_bounds__(1024) void block_conv_kernel(const BlockArgs a) {
                 o[e] = fminf(fmaxf(z, lo), hi);
               } else {  // v1: cotangent of BN's output, v2: BN's input, v3: BN's output where a residual went into it
                 const float xc = v2[u][e] - mu[e], y = has3 ? v3[u][e] : fmaf(xc, sc[e], be[e]);
-                const float dz = (b.act == S4TF_ACT_NONE || (y > 0.f && y < hi)) ? v1[u][e] : 0.f;
+                const float dz = (no_act | ((y > 0.f) & (y < hi))) ? v1[u][e] : 0.f;  // (bitwise: no branches)
                 r[e] = dz;
                 o[e] = fmaf(sc[e], dz, -fmaf(xc, a2[e], a0[e]));
               }
@@ -421,6 +422,7 @@ __global__ __launch_bounds__(1024) void block_conv_kernel(const BlockArgs a) {
       if (!b.ny) { sc = b.ngamma[col] * is; be = b.nbeta[col]; }
     }
     const float hi = b.nact == S4TF_ACT_RELU6 ? 6.f : __builtin_inff();
+    const bool no_nact = b.nact == S4TF_ACT_NONE;
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll
@@ -430,7 +432,7 @@ __global__ __launch_bounds__(1024) void block_conv_kernel(const BlockArgs a) {
         if (m < live) {
           b.out[out0 + (long long)m * KT] = val;
           const float xc = nz[g][v] - mu, y = b.ny ? ny[g][v] : fmaf(xc, sc, be);
-          const float dz = (b.nact == S4TF_ACT_NONE || (y > 0.f && y < hi)) ? val : 0.f;
+          const float dz = (no_nact | ((y > 0.f) & (y < hi))) ? val : 0.f;
           s += dz;
           q += dz * (xc * is);
         }
