@@ -335,7 +335,7 @@ __device__ __forceinline__ void bn_apply_body(const T* __restrict__ x, const T* 
   walk_pixels(p0 + pl, p1, pl_count,
               [&](long long m, int u) {
                 xv[u] = ldp<T, V>(x + m * C + c);
-                if (res) rv[u] = ldp<T, V>(res + m * C + c);
+                if (res) rv[u] = ldp_once<T, V>(res + m * C + c);  // (x is what the pullback reads first)
               },
               [&](long long m, int u) {
                 float o[V];
@@ -372,13 +372,13 @@ template <typename T, int V> __global__ __launch_bounds__(256) void bn_apply_inf
 // that double accumulators would hold through the loop are what lets a fourth wavefront share a SIMD
 // (the kernel is bound by how many loads it keeps in flight: 898 -> 750 us over the BatchNorms of a
 // ResNet-50).
-template <typename T, int V, bool REMASK, bool BITS = false>
+template <typename T, int V, bool REMASK, bool BITS = false, bool WRES = false>
 __device__ __forceinline__ void bn_vjp_reduce_body(const T* __restrict__ x, const T* __restrict__ y,
                                                    const T* __restrict__ dy, const float* __restrict__ mean,
                                                    const float* __restrict__ invstd, const float* __restrict__ gamma,
                                                    const float* __restrict__ beta, double* __restrict__ part,
                                                    long long M, int C, int cvb, long long per, int act,
-                                                   const unsigned char* __restrict__ bits = nullptr) {
+                                                   const unsigned char* __restrict__ bits = nullptr, T* dres = nullptr) {
   extern __shared__ double redd[];
   const int CV = C / V, pl_count = blockDim.x / cvb;
   const int cvl = threadIdx.x % cvb, pl = threadIdx.x / cvb;
@@ -408,11 +408,12 @@ __device__ __forceinline__ void bn_vjp_reduce_body(const T* __restrict__ x, cons
     walk_pixels(p0 + pl, p1, pl_count,
                 [&](long long m, int u) {
                   xv[u] = ldp<T, V>(x + m * C + c);
-                  dv[u] = ldp<T, V>(dy + m * C + c);
+                  dv[u] = WRES ? ldp_once<T, V>(dy + m * C + c) : ldp<T, V>(dy + m * C + c);
                   if (BITS) bv[u] = bits[m * CV + cv];
-                  else if (act != S4TF_ACT_NONE && !remask) yv[u] = ldp<T, V>(y + m * C + c);
+                  else if (act != S4TF_ACT_NONE && !remask) yv[u] = WRES ? ldp_once<T, V>(y + m * C + c) : ldp<T, V>(y + m * C + c);
                 },
-                [&](long long, int u) {
+                [&](long long m, int u) {
+                  float r[V];
 #pragma unroll
                   for (int e = 0; e < V; ++e) {
                     float dz = dv[u].get(e);
@@ -427,7 +428,9 @@ __device__ __forceinline__ void bn_vjp_reduce_body(const T* __restrict__ x, cons
                     }
                     grp[e] += dz;
                     grp[V + e] += dz * ((xv[u].get(e) - mu[e]) * is[e]);
+                    r[e] = dz;
                   }
+                  if (WRES) stp<T, V>(dres + m * C + c, pack_of<T, V>(r));
                 });
   }
   // lanes of a wavefront that share a channel vector: a butterfly in fp32 (a tree over at most 64 thread sums);
@@ -465,6 +468,18 @@ template <typename T, int V> __global__ __launch_bounds__(256) void bn_vjp_reduc
                                         reinterpret_cast<const unsigned char*>(y));
 }
 
+// The same two, storing dz on the way: it is the residual's cotangent, and what the second pass then reads instead of dy and the
+// activation's output (7 tensors moved in all instead of 8).  dy and the output are not read again: loaded so that they leave
+// x and dz in the last-level cache.  64 x 56 x 56 x 256 bf16, us: sums 65 -> 64, second pass 82 -> 52 with its order turned round
+// (bn_vjp_apply_body); with ordinary loads 75.
+template <typename T, int V> __global__ __launch_bounds__(256) void bn_vjp_reduce_dres_kernel(BN_VJP_REDUCE_ARGS, T* dres) {
+  bn_vjp_reduce_body<T, V, false, false, true>(x, y, dy, mean, invstd, gamma, beta, part, M, C, cvb, per, act, nullptr, dres);
+}
+template <typename T, int V> __global__ __launch_bounds__(256) void bn_vjp_reduce_bits_dres_kernel(BN_VJP_REDUCE_ARGS, T* dres) {
+  bn_vjp_reduce_body<T, V, false, true, true>(x, nullptr, dy, mean, invstd, gamma, beta, part, M, C, cvb, per, act,
+                                              reinterpret_cast<const unsigned char*>(y), dres);
+}
+
 __global__ __launch_bounds__(FIN_THREADS) void bn_vjp_finalize_kernel(const double* __restrict__ part, int chunks, int C,
                                                                       float* __restrict__ dgamma, float* __restrict__ dbeta) {
   __shared__ double sh[FIN_THREADS / 64][2][8];
@@ -483,7 +498,7 @@ __device__ __forceinline__ void bn_vjp_apply_body(const T* __restrict__ x, const
                                                            const float* __restrict__ beta,
                                                            const float* __restrict__ dgamma, const float* __restrict__ dbeta,
                                                            T* __restrict__ dx, T* dres, int acc_dres, long long M, int C,
-                                                           int cvb, long long per, int act,
+                                                           int cvb, long long per, long long per_r, int pieces, int act,
                                                            const unsigned char* __restrict__ bits = nullptr) {
   const int CV = C / V, pl_count = blockDim.x / cvb;
   const int cvl = threadIdx.x % cvb, pl = threadIdx.x / cvb;
@@ -506,7 +521,11 @@ __device__ __forceinline__ void bn_vjp_apply_body(const T* __restrict__ x, const
     a0[e] = gs[e] * (dbeta[c + e] * invM);
     a2[e] = gs[e] * (is * (dgamma[c + e] * invM));
   }
-  const long long p0 = (long long)blockIdx.y * per, p1 = p0 + per < M ? p0 + per : M;
+  // The sums' chunks of per_r pixels, all walked at the same time before, in `pieces` pieces: the last piece of every chunk
+  // first, so that a tensor too large for the last-level cache (256 MB) is read while its end is still there
+  const int chunks = gridDim.y / pieces, piece = pieces - 1 - (int)blockIdx.y / chunks;
+  const long long q0 = (long long)((int)blockIdx.y % chunks) * per_r, q1 = q0 + per_r < M ? q0 + per_r : M;
+  const long long p0 = q0 + piece * per, p1 = p0 + per < q1 ? p0 + per : q1;
   Pack<T, V> xv[UNROLL], dv[UNROLL], yv[UNROLL], ov[UNROLL], av[UNROLL];
   unsigned char bv[UNROLL];
   walk_pixels(p0 + pl, p1, pl_count,
@@ -545,27 +564,27 @@ __device__ __forceinline__ void bn_vjp_apply_body(const T* __restrict__ x, const
   const T *__restrict__ x, const T *__restrict__ y, const T *__restrict__ dy, const float *__restrict__ gamma,       \
       const float *__restrict__ mean, const float *__restrict__ invstd, const float *__restrict__ beta,              \
       const float *__restrict__ dgamma, const float *__restrict__ dbeta, T *__restrict__ dx, T *dres, int acc_dres,  \
-      long long M, int C, int cvb, long long per, int act
+      long long M, int C, int cvb, long long per, long long per_r, int pieces, int act
 template <typename T, int V> __global__ __launch_bounds__(256) void bn_vjp_apply_kernel(BN_VJP_APPLY_ARGS) {
-  bn_vjp_apply_body<T, V, false>(x, y, dy, gamma, mean, invstd, beta, dgamma, dbeta, dx, dres, acc_dres, M, C, cvb, per, act);
+  bn_vjp_apply_body<T, V, false>(x, y, dy, gamma, mean, invstd, beta, dgamma, dbeta, dx, dres, acc_dres, M, C, cvb, per, per_r, pieces, act);
 }
 template <typename T, int V> __global__ __launch_bounds__(256) void bn_vjp_apply_remask_kernel(BN_VJP_APPLY_ARGS) {
-  bn_vjp_apply_body<T, V, true>(x, y, dy, gamma, mean, invstd, beta, dgamma, dbeta, dx, dres, acc_dres, M, C, cvb, per, act);
+  bn_vjp_apply_body<T, V, true>(x, y, dy, gamma, mean, invstd, beta, dgamma, dbeta, dx, dres, acc_dres, M, C, cvb, per, per_r, pieces, act);
 }
 template <typename T, int V> __global__ __launch_bounds__(256) void bn_vjp_apply_bits_kernel(BN_VJP_APPLY_ARGS) {
   bn_vjp_apply_body<T, V, false, true>(x, nullptr, dy, gamma, mean, invstd, beta, dgamma, dbeta, dx, dres, acc_dres, M, C,
-                                       cvb, per, act, reinterpret_cast<const unsigned char*>(y));
+                                       cvb, per, per_r, pieces, act, reinterpret_cast<const unsigned char*>(y));
 }
 // the same three, adding into the cotangent dx already holds (separate instances: the plain ones keep their registers)
 template <typename T, int V> __global__ __launch_bounds__(256) void bn_vjp_apply_acc_kernel(BN_VJP_APPLY_ARGS) {
-  bn_vjp_apply_body<T, V, false, false, true>(x, y, dy, gamma, mean, invstd, beta, dgamma, dbeta, dx, dres, acc_dres, M, C, cvb, per, act);
+  bn_vjp_apply_body<T, V, false, false, true>(x, y, dy, gamma, mean, invstd, beta, dgamma, dbeta, dx, dres, acc_dres, M, C, cvb, per, per_r, pieces, act);
 }
 template <typename T, int V> __global__ __launch_bounds__(256) void bn_vjp_apply_remask_acc_kernel(BN_VJP_APPLY_ARGS) {
-  bn_vjp_apply_body<T, V, true, false, true>(x, y, dy, gamma, mean, invstd, beta, dgamma, dbeta, dx, dres, acc_dres, M, C, cvb, per, act);
+  bn_vjp_apply_body<T, V, true, false, true>(x, y, dy, gamma, mean, invstd, beta, dgamma, dbeta, dx, dres, acc_dres, M, C, cvb, per, per_r, pieces, act);
 }
 template <typename T, int V> __global__ __launch_bounds__(256) void bn_vjp_apply_bits_acc_kernel(BN_VJP_APPLY_ARGS) {
   bn_vjp_apply_body<T, V, false, true, true>(x, nullptr, dy, gamma, mean, invstd, beta, dgamma, dbeta, dx, dres, acc_dres, M, C,
-                                             cvb, per, act, reinterpret_cast<const unsigned char*>(y));
+                                             cvb, per, per_r, pieces, act, reinterpret_cast<const unsigned char*>(y));
 }
 
 // ---- layers small enough for the sums to be finished inside the kernel that uses them -----------------------------
@@ -1260,7 +1279,12 @@ int bn_vjp(const s4tf_bn_desc& d, const void* x, const void* y, const float* gam
   if (beta || d.act == S4TF_ACT_NONE) maskbits = nullptr;
   if (maskbits) y = maskbits;  // the bits kernels take them through the y argument
   const Plan pr = make_plan((size_t)M, C, d.dtype, 512, UNROLL);  // measured over the ResNet-50 shapes: 512 blocks beat 1024 and 256
-  const Plan pa = make_plan((size_t)M, C, d.dtype, 2048, UNROLL);
+  // the second pass's blocks: about 2048, whole pieces of the first one's chunks
+  Plan pa = make_plan((size_t)M, C, d.dtype, 2048, UNROLL);
+  const int pieces = pa.chunks > pr.chunks ? (pa.chunks + pr.chunks - 1) / pr.chunks : 1;
+  pa.per = (pr.per + pieces - 1) / pieces;
+  pa.chunks = pr.chunks * pieces;
+  const bool early_dres = dres && !d.accumulate_dres && d.act != S4TF_ACT_NONE && !beta;
   double* part = static_cast<double*>(ws);
   int rc;
   if (C % pr.V == 0 && pr.V > 1) {
@@ -1289,7 +1313,13 @@ int bn_vjp(const s4tf_bn_desc& d, const void* x, const void* y, const float* gam
   }
   {
     ProfScope ps(PC_BN_VJP_REDUCE, st);
-    if (maskbits)
+    if (early_dres && maskbits)
+      BN_LAUNCH(bn_vjp_reduce_bits_dres_kernel, pr, (size_t)4 * pr.cvb * 2 * pr.V * sizeof(double), (const T*)x, (const T*)y,
+                (const T*)dy, mean, invstd, gamma, beta, part, M, C, pr.cvb, pr.per, d.act, (T*)dres);
+    else if (early_dres)
+      BN_LAUNCH(bn_vjp_reduce_dres_kernel, pr, (size_t)4 * pr.cvb * 2 * pr.V * sizeof(double), (const T*)x, (const T*)y,
+                (const T*)dy, mean, invstd, gamma, beta, part, M, C, pr.cvb, pr.per, d.act, (T*)dres);
+    else if (maskbits)
       BN_LAUNCH(bn_vjp_reduce_bits_kernel, pr, (size_t)4 * pr.cvb * 2 * pr.V * sizeof(double), (const T*)x, (const T*)y,
                 (const T*)dy, mean, invstd, gamma, beta, part, M, C, pr.cvb, pr.per, d.act);
     else if (beta)
@@ -1302,28 +1332,35 @@ int bn_vjp(const s4tf_bn_desc& d, const void* x, const void* y, const float* gam
     hipLaunchKernelGGL(bn_vjp_finalize_kernel, dim3((C + 7) / 8), dim3(FIN_THREADS), 0, st, part, pr.chunks, C, dgamma, dbeta);
     if ((rc = launch_status("bn_vjp_finalize")) != S4TF_OK) return rc;
   }
+  int act = d.act;
+  if (early_dres) {  // dres holds dz
+    dy = dres;
+    dres = nullptr;
+    maskbits = nullptr;
+    act = S4TF_ACT_NONE;
+  }
   ProfScope ps(PC_BN_VJP_APPLY, st);
   if (d.accumulate_dx) {
     if (maskbits)
       BN_LAUNCH(bn_vjp_apply_bits_acc_kernel, pa, 0, (const T*)x, (const T*)y, (const T*)dy, gamma, mean, invstd, beta, dgamma, dbeta,
-                (T*)dx, (T*)dres, d.accumulate_dres, M, C, pa.cvb, pa.per, d.act);
+                (T*)dx, (T*)dres, d.accumulate_dres, M, C, pa.cvb, pa.per, pr.per, pieces, act);
     else if (beta)
       BN_LAUNCH(bn_vjp_apply_remask_acc_kernel, pa, 0, (const T*)x, (const T*)y, (const T*)dy, gamma, mean, invstd, beta, dgamma, dbeta,
-                (T*)dx, (T*)dres, d.accumulate_dres, M, C, pa.cvb, pa.per, d.act);
+                (T*)dx, (T*)dres, d.accumulate_dres, M, C, pa.cvb, pa.per, pr.per, pieces, act);
     else
       BN_LAUNCH(bn_vjp_apply_acc_kernel, pa, 0, (const T*)x, (const T*)y, (const T*)dy, gamma, mean, invstd, beta, dgamma, dbeta,
-                (T*)dx, (T*)dres, d.accumulate_dres, M, C, pa.cvb, pa.per, d.act);
+                (T*)dx, (T*)dres, d.accumulate_dres, M, C, pa.cvb, pa.per, pr.per, pieces, act);
     return launch_status("bn_vjp_apply");
   }
   if (maskbits)
     BN_LAUNCH(bn_vjp_apply_bits_kernel, pa, 0, (const T*)x, (const T*)y, (const T*)dy, gamma, mean, invstd, beta, dgamma, dbeta,
-              (T*)dx, (T*)dres, d.accumulate_dres, M, C, pa.cvb, pa.per, d.act);
+              (T*)dx, (T*)dres, d.accumulate_dres, M, C, pa.cvb, pa.per, pr.per, pieces, act);
   else if (beta)
     BN_LAUNCH(bn_vjp_apply_remask_kernel, pa, 0, (const T*)x, (const T*)y, (const T*)dy, gamma, mean, invstd, beta, dgamma, dbeta,
-              (T*)dx, (T*)dres, d.accumulate_dres, M, C, pa.cvb, pa.per, d.act);
+              (T*)dx, (T*)dres, d.accumulate_dres, M, C, pa.cvb, pa.per, pr.per, pieces, act);
   else
     BN_LAUNCH(bn_vjp_apply_kernel, pa, 0, (const T*)x, (const T*)y, (const T*)dy, gamma, mean, invstd, beta, dgamma, dbeta,
-              (T*)dx, (T*)dres, d.accumulate_dres, M, C, pa.cvb, pa.per, d.act);
+              (T*)dx, (T*)dres, d.accumulate_dres, M, C, pa.cvb, pa.per, pr.per, pieces, act);
   return launch_status("bn_vjp_apply");
 }
 

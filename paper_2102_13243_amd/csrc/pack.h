@@ -59,6 +59,15 @@ template <> __device__ inline Pack<bf16_t, 8> pack_of<bf16_t, 8>(const float (&v
 template <typename T, int V> __device__ inline Pack<T, V> ldp(const T* p) {
   return *reinterpret_cast<const Pack<T, V>*>(p);
 }
+// the same for data nobody reads again soon: it does not push other data out of the last-level cache
+template <typename T, int V> __device__ inline Pack<T, V> ldp_once(const T* p) {
+  if constexpr (sizeof(Pack<T, V>) == 16) {
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(Pack<T, V>, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
+  } else {
+    return ldp<T, V>(p);
+  }
+}
 template <typename T, int V> __device__ inline void stp(T* p, const Pack<T, V>& v) {
   *reinterpret_cast<Pack<T, V>*>(p) = v;
 }

@@ -409,6 +409,15 @@ def test_bn_small_layers(shape, act, use_res, bf16):
 
 
 @pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
+@pytest.mark.parametrize("act,use_res", [("relu", True), ("relu6", False)])
+@pytest.mark.parametrize("shape", [(3, 61, 67, 136), (9, 53, 129, 136), (7, 41, 43, 20), (1, 1, 3, 20)], ids=lambda s: "x".join(map(str, s)))
+def test_bn_pullback_in_pieces(shape, act, use_res, bf16):
+    """The two passes over tensors too large for the other kernels, or with channels in no whole vectors: the second walks
+    the chunks of the first in pieces, last piece first, and reads what the first stored for the residual."""
+    test_bn_relu_fwd_and_vjp(shape, act, use_res, bf16)
+
+
+@pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
 @pytest.mark.parametrize("act,use_res", [("none", False), ("relu", False), ("relu", True), ("relu6", True)])
 @pytest.mark.parametrize("shape", BN_SHAPES, ids=lambda s: "x".join(map(str, s)))
 def test_bn_relu_fwd_and_vjp(shape, act, use_res, bf16):
