@@ -125,7 +125,7 @@ static size_t conv_vjp_ws_parts(const s4tf_conv_desc& d, size_t* dz_bytes) {
   ConvGeom g = conv_geom(d);
   size_t dz = d.act != S4TF_ACT_NONE ? align_up((size_t)g.N * g.P * g.Q * g.K * dtype_size(d.dtype), 256) : 0;
   if (dz_bytes) *dz_bytes = dz;
-  size_t wg = d.groups == 1 ? igemm_wgrad_workspace(g, d.dtype) : dwconv_wgrad_workspace(g);
+  size_t wg = d.groups == 1 ? igemm_wgrad_workspace(g, d.dtype, true) : dwconv_wgrad_workspace(g);
   const size_t cs = colsum_workspace((size_t)g.N * g.P * g.Q, g.K);  // bias gradient: used before the filter gradient, same bytes
   if (cs > wg) wg = cs;
   return dz + align_up(wg, 256);
@@ -148,16 +148,16 @@ int conv_dgrad_impl(const s4tf_conv_desc& d, const void* w, const void* dz, void
   return dwconv_dgrad(g, d.dtype, dz, w, dx, d.accumulate_dx, st);
 }
 int conv_param_grads_impl(const s4tf_conv_desc& d, const void* x, const void* dz, float* dw, float* dbias,
-                          void* wg_ws, size_t wg_bytes, hipStream_t st) {
+                          void* wg_ws, size_t wg_bytes, hipStream_t st, bool alone) {
   ConvGeom g = conv_geom(d);
-  if (d.groups == 1) return igemm_wgrad(g, d.dtype, x, dz, dw, wg_ws, wg_bytes, st, dbias);
+  if (d.groups == 1) return igemm_wgrad(g, d.dtype, x, dz, dw, wg_ws, wg_bytes, st, dbias, alone);
   if (dbias) CHECK(colsum(d.dtype, dz, (size_t)g.N * g.P * g.Q, g.K, dbias, st, wg_ws, wg_bytes));
   return dwconv_wgrad(g, d.dtype, x, dz, dw, wg_ws, st);
 }
 static int conv_vjp_impl(const s4tf_conv_desc& d, const void* x, const void* w, const void* dz, void* dx, float* dw,
                          float* dbias, void* wg_ws, size_t wg_bytes, hipStream_t st) {
   if (dx) CHECK(conv_dgrad_impl(d, w, dz, dx, st));
-  return conv_param_grads_impl(d, x, dz, dw, dbias, wg_ws, wg_bytes, st);
+  return conv_param_grads_impl(d, x, dz, dw, dbias, wg_ws, wg_bytes, st, true);
 }
 
 // What s4tf_profile_bracket_overhead brackets: one wavefront that waits until the constant-rate (100 MHz)

@@ -21,7 +21,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 template <typename T> struct Cfg;
-template <> struct Cfg<float> { static constexpr int VEC = 4, BK = 16, PAD = 1; };
+template <> struct Cfg<float> { static constexpr int VEC = 4, PAD = 1; };
 template <> struct Cfg<bf16_t> { static constexpr int VEC = 8, BK = 64, PAD = 8; };
 
 __device__ inline uint4 ldg16(const void* p) { return *reinterpret_cast<const uint4*>(p); }
@@ -1011,17 +1011,18 @@ int igemm_dgrad(const ConvGeom& g, int dtype, const void* dy, const void* w, voi
   return launch<float, PASS_DGRAD>(a, 1, st);
 }
 
-size_t igemm_wgrad_workspace(const ConvGeom& g, int dtype) {
+size_t igemm_wgrad_workspace(const ConvGeom& g, int dtype, bool alone) {
   if (small_conv_ok(PASS_WGRAD, g, dtype)) return small_wgrad_workspace(g);
   int splits, per;
   if (wave_gemm_ok(PASS_WGRAD, g, dtype)) splits = wave_gemm_wgrad_splits(g);
   else wgrad_split(g, dtype, splits, per);
+  if (alone && wgrad3_ok(g, dtype) && wgrad3_splits(g) > splits) splits = wgrad3_splits(g);
   if (splits <= 1) return 0;
   return (size_t)splits * g.R * g.S * g.C * g.K * sizeof(float);
 }
 
 int igemm_wgrad(const ConvGeom& g, int dtype, const void* x, const void* dy, float* dw, void* ws,
-                size_t ws_bytes, hipStream_t st, float* db) {
+                size_t ws_bytes, hipStream_t st, float* db, bool alone) {
   if (small_conv_ok(PASS_WGRAD, g, dtype)) {
     const size_t need = small_wgrad_workspace(g);
     if (ws_bytes < need) return fail(S4TF_ERR_WORKSPACE, "wgrad needs %zu workspace bytes, got %zu", need, ws_bytes);
@@ -1033,8 +1034,12 @@ int igemm_wgrad(const ConvGeom& g, int dtype, const void* x, const void* dy, flo
   a.simple = (g.R == 1 && g.S == 1 && g.stride == 1 && g.pad == 0);
   fill_sizes(a, PASS_WGRAD, dtype);
   const bool waves = wave_gemm_ok(PASS_WGRAD, g, dtype) && aligned16(x) && aligned16(dy) && aligned16(dw) && aligned16(ws);
+  // The band kernel takes most of a CU's LDS.  By itself it is the faster one; beside the input cotangents on the step's other
+  // stream, whose workgroups it keeps out, it is not (ResNet-50 at batch 64: 6.81 ms with the general kernel, 6.91 with it).
+  const bool three = alone && wgrad3_ok(g, dtype) && aligned16(x) && aligned16(dy);
   int splits, per = 0;
   if (waves) splits = wave_gemm_wgrad_splits(g);
+  else if (three) splits = wgrad3_splits(g);
   else wgrad_split(g, dtype, splits, per);
   const long long n = (long long)a.Mg * a.Ng;
   const bool with_bias = waves && wave_gemm_bias_ok(g);
@@ -1048,6 +1053,9 @@ int igemm_wgrad(const ConvGeom& g, int dtype, const void* x, const void* dy, flo
   if (waves) {
     ProfScope ps(PC_CONV_WGRAD, st);
     rc = wave_gemm_wgrad(g, static_cast<const float*>(x), static_cast<const float*>(dy), splits > 1 ? static_cast<float*>(ws) : dw, with_bias ? db : nullptr, st);
+  } else if (three) {
+    ProfScope ps(PC_CONV_WGRAD, st);
+    rc = wgrad3(g, x, dy, splits > 1 ? static_cast<float*>(ws) : dw, st);
   } else {
     if (dtype == S4TF_BF16) fill_tiles(a, 128, 128, Cfg<bf16_t>::BK);
     else fill_tiles_f32(a, true);

@@ -84,6 +84,11 @@ bool igemm_dma_ok(int pass, const ConvGeom& g, const Args& a);            // sha
 void igemm_dma_tile(int pass, int Mg, int Ng, int splits, int& BM, int& BN);  // the tile igemm_dma_launch picks
 int igemm_dma_launch(int pass, Args& a, int splits, hipStream_t st);
 
+// bf16 filter gradients of 3x3 / stride 1 / padding 1 layers (wgrad3.hip)
+bool wgrad3_ok(const ConvGeom& g, int dtype);
+int wgrad3_splits(const ConvGeom& g);
+int wgrad3(const ConvGeom& g, const void* x, const void* dy, float* out, hipStream_t st);
+
 // fp32, channel counts that are multiples of 4 (wave_gemm.hip)
 bool wave_gemm_ok(int pass, const ConvGeom& g, int dtype);
 int wave_gemm_fwd(const ConvGeom& g, const float* x, const float* w, const float* bias, int act, float* y, float* stats,

@@ -122,9 +122,10 @@ bool igemm_dgrad_can_mask(const ConvGeom& g, int dtype);
 bool igemm_dgrad_adds_other(const ConvGeom& g, int dtype, const void* dy, const void* w, const void* dx,
                             const void* acc_src);
 bool igemm_dgrad_can_add_other(const ConvGeom& g, int dtype);  // the same question for 16-byte aligned operands
-size_t igemm_wgrad_workspace(const ConvGeom& g, int dtype);
+size_t igemm_wgrad_workspace(const ConvGeom& g, int dtype, bool alone = false);
 int igemm_wgrad(const ConvGeom& g, int dtype, const void* x, const void* dy, float* dw, void* ws,
-                size_t ws_bytes, hipStream_t st, float* db = nullptr);  // db: also the column sums of dy, the bias gradient
+                size_t ws_bytes, hipStream_t st, float* db = nullptr,  // db: also the column sums of dy, the bias gradient
+                bool alone = false);  // no other stream's kernels run beside it
 
 // depthwise (groups == C == K)
 int dwconv_fwd(const ConvGeom& g, int dtype, const void* x, const void* w, const float* bias, int act,
@@ -242,7 +243,7 @@ int conv_dgrad_impl(const s4tf_conv_desc& d, const void* w, const void* dz, void
                     const void* acc_src = nullptr, const unsigned char* acc_bits = nullptr, const void* mask = nullptr,
                     int mask_act = S4TF_ACT_NONE);
 int conv_param_grads_impl(const s4tf_conv_desc& d, const void* x, const void* dz, float* dw, float* dbias,
-                          void* wg_ws, size_t wg_bytes, hipStream_t st);
+                          void* wg_ws, size_t wg_bytes, hipStream_t st, bool alone = false);
 
 inline int launch_status(const char* what) {
   hipError_t e = hipGetLastError();

@@ -219,6 +219,19 @@ def test_conv2d_bands(shape):
     test_conv2d_fwd_and_vjp(shape, False)
 
 
+# bf16 3x3 filter gradients at the edges of the band kernel: the widest row that fits, one column, single pixels, several
+# images in a band with a rest, a last band with fewer rows, several blocks of 32 channels either way
+WGRAD3_SHAPES = [
+    (2, 2, 240, 32, 32, 3, 1, 1), (9, 60, 1, 32, 64, 3, 1, 1), (600, 1, 1, 32, 32, 3, 1, 1), (33, 4, 4, 64, 32, 3, 1, 1),
+    (2, 37, 23, 32, 96, 3, 1, 1), (21, 7, 7, 96, 64, 3, 1, 1),
+]
+
+
+@pytest.mark.parametrize("shape", WGRAD3_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_conv2d_filter_gradient_bands(shape):
+    test_conv2d_fwd_and_vjp(shape, True)
+
+
 def _random_conv_shapes(count, seed):
     """Seeded shapes drawn from the values at which the library switches kernels (channel counts around the
     loaders' vector widths and the LDS-patch kernel's 16/24/32/64, image sizes around its 8/16/32-wide tiles,
